@@ -160,7 +160,9 @@ __global__ __launch_bounds__(256, 4) void conv_lds_kernel(SpmmArgs p, ConvLdsSch
     uint32_t av[R][RT][KS][F::VW], aw[R][RT][F::WPR];
     const bool busy = works && cnt > 0;
     auto block_of = [&](int entry_index) __attribute__((always_inline)) {
-        const uint32_t en = ord[wave][min(entry_index, CONV_LDS_ORD - 1)];
+        // (the entry is the same in every lane: made uniform, so that the block's offset is a scalar operand of its
+        // requests; left in a vector register, every request became a loop over the lanes' values)
+        const uint32_t en = (uint32_t)__builtin_amdgcn_readfirstlane((int)ord[wave][min(entry_index, CONV_LDS_ORD - 1)]);
         return t_begin + (int)((en >> 16) & 0x7FFFu);
     };
     int e = 0;
