@@ -409,27 +409,33 @@ __device__ __forceinline__ void smf_operand(const uint32_t (&av)[Fmt<N, M, B>::K
             for (int i = 0; i < 8; ++i) idx |= ((field >> (3 * i)) & 3u) << (2 * i);
         } else if constexpr (N == 2) {
             // group g: stored (v0, v1) at positions (p0, p1); the lower 4-group takes those with
-            // position < 4, the upper the others, both with in-group positions (p0 & 3, p1 & 3)
+            // position < 4, the upper the others, both with in-group positions (p0 & 3, p1 & 3).
+            // Bit 2 of a position, spread over a word by a signed bit-field extract, is the mask of its half.
             uint32_t d[4];
-            idx = 0;
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
                 const uint32_t w = av[2 * s2 + g][0];
-                const uint32_t p0 = (field >> (6 * g)) & 7u, p1 = (field >> (6 * g + 3)) & 7u;
-                const uint32_t lowmask = ((p0 & 4u) ? 0u : 0x0000FFFFu) | ((p1 & 4u) ? 0u : 0xFFFF0000u);
-                d[2 * g] = w & lowmask;
-                d[2 * g + 1] = w & ~lowmask;
-                const uint32_t nib = (p0 & 3u) | ((p1 & 3u) << 2);
-                idx |= (nib | (nib << 4)) << (8 * g);
+                const uint32_t up0 = (uint32_t)__builtin_amdgcn_sbfe((int)field, 6 * g + 2, 1);
+                const uint32_t up1 = (uint32_t)__builtin_amdgcn_sbfe((int)field, 6 * g + 5, 1);
+                const uint32_t hi = w & ((up0 & 0xFFFFu) | (up1 & 0xFFFF0000u));
+                d[2 * g] = w ^ hi;
+                d[2 * g + 1] = hi;
             }
             a4 = u32x4{d[0], d[1], d[2], d[3]};
+            // both groups' index nibbles at once: p0 & 3 and p1 & 3 side by side at bits 0..3 and 6..9, the second
+            // group's moved up to bit 8, then every nibble doubled (only bits 0..15 are read by the instruction)
+            const uint32_t pairs = ((field & 0x0C3u) | ((field >> 1) & ~0x0C3u)) & 0x3CFu;
+            const uint32_t nibs = (pairs & 0xFu) | ((pairs << 2) & 0xF00u);
+            idx = nibs | (nibs << 4);
         } else {
             // one stored value per group of 8, paired with a zero at the same position
             const uint32_t va = av[2 * s2][0], vb2 = av[2 * s2 + 1][0];
-            const uint32_t pa = field & 7u, pb = (field >> 3) & 7u;
-            a4 = u32x4{(pa & 4u) ? 0u : va, (pa & 4u) ? va : 0u, (pb & 4u) ? 0u : vb2, (pb & 4u) ? vb2 : 0u};
-            const uint32_t na = (pa & 3u) * 5u, nb = (pb & 3u) * 5u;     // (p, p) as a nibble
-            idx = (na | (na << 4)) | ((nb | (nb << 4)) << 8);
+            const uint32_t ha = va & (uint32_t)__builtin_amdgcn_sbfe((int)field, 2, 1);
+            const uint32_t hb = vb2 & (uint32_t)__builtin_amdgcn_sbfe((int)field, 5, 1);
+            a4 = u32x4{va ^ ha, ha, vb2 ^ hb, hb};
+            // positions at bits 0..1 and 8..9, then each repeated four times
+            const uint32_t two = (field & 3u) | ((field << 5) & 0x300u);
+            idx = two * 0x55u;
         }
     } else if constexpr (N == 2) {
         // 2:4: values and positions as packed
