@@ -30,7 +30,8 @@ constexpr int XLDS_LIST = 512;          // block-list entries of a group staged 
 // activation [C][batch][H][W]: K-row c is channel c, and the lane's two columns are elements 0 and 2 of one
 // 8-byte piece of input row 2 * oh, so the strided gather is done once per strip here instead of once per
 // block-row.
-template <int N, int M, bool SMF, int CONV>
+// PRES: bf16 output with a residual that is requested ahead across block-rows (ResidualStream).
+template <int N, int M, bool SMF, int CONV, bool PRES>
 __global__ __launch_bounds__(256, 4) void spmm_xlds_kernel(SpmmArgs p, int rows_per_group, int row_groups, int Kb) {
     static_assert(CONV == 0 || CONV == 4, "plain X or the strided 1 x 1 lowering");
     constexpr int B = 64;
@@ -208,6 +209,8 @@ __global__ __launch_bounds__(256, 4) void spmm_xlds_kernel(SpmmArgs p, int rows_
         const int tf = next_block_from(bi0 + wave);
         if (tf < t1) Body::load_a(av, aw, p, a_off, i_off, tf);
     }
+    ResidualStream<2> rs;
+    if constexpr (PRES) rs.start(p, min(bi0 + wave, bi1), bi1, hh, lane, col0, col_ok);
     for (int bi = bi0 + wave; bi < bi1; bi += 4) {
         const int t_begin = __builtin_amdgcn_readlane(my_ptr, bi - bi0);
         const int t_end = __builtin_amdgcn_readlane(my_ptr, bi + 1 - bi0);
@@ -225,6 +228,10 @@ __global__ __launch_bounds__(256, 4) void spmm_xlds_kernel(SpmmArgs p, int rows_
         }
         int hh_now = hh;
         asm volatile("" : "+v"(hh_now));
+        if constexpr (PRES) {
+            rs.store(p, bi, bi + 4, bi1, hh_now, lane, col0, col_ok, acc);
+            continue;
+        }
 #pragma unroll
         for (int r0 = 0; r0 < RT * 16; r0 += 8)
             store_rows<B, 1, 8, 1>(p, bi, hh_now, col0, col_ok, r0, [&](int pr, float (&v)[NACC]) __attribute__((always_inline)) {
@@ -243,7 +250,7 @@ inline bool xlds_covers(const SpmmArgs& a, int B) {
            a.ldy <= ((int64_t)1 << 23) && !(a.ep_on && a.ep_res && a.ep_ldr > ((int64_t)1 << 23));
 }
 
-template <int N, int M, bool SMF, int CONV>
+template <int N, int M, bool SMF, int CONV, bool PRES>
 hipError_t launch_xlds_k(const SpmmArgs& a, hipStream_t st) {
     const int Kb = (a.K + 63) / 64;
     const int64_t strips = (a.Ncol + 63) / 64;
@@ -263,7 +270,7 @@ hipError_t launch_xlds_k(const SpmmArgs& a, hipStream_t st) {
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
         if (!(raised.load() >> dev & 1)) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&spmm_xlds_kernel<N, M, SMF, CONV>),
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&spmm_xlds_kernel<N, M, SMF, CONV, PRES>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, XLDS_MAX_KB * 8192 + XLDS_LIST * 4);
             if (e != hipSuccess) return e;
             raised.fetch_or((uint64_t)1 << dev);
@@ -271,19 +278,25 @@ hipError_t launch_xlds_k(const SpmmArgs& a, hipStream_t st) {
     }
     const dim3 grd((unsigned)wgs), blk(256);
     if (a.ev_start || a.ev_stop)
-        hipExtLaunchKernelGGL((spmm_xlds_kernel<N, M, SMF, CONV>), grd, blk, lds, st, a.ev_start, a.ev_stop, 0, a, rpg, row_groups, Kb);
+        hipExtLaunchKernelGGL((spmm_xlds_kernel<N, M, SMF, CONV, PRES>), grd, blk, lds, st, a.ev_start, a.ev_stop, 0, a, rpg, row_groups, Kb);
     else
-        spmm_xlds_kernel<N, M, SMF, CONV><<<grd, blk, lds, st>>>(a, rpg, row_groups, Kb);
+        spmm_xlds_kernel<N, M, SMF, CONV, PRES><<<grd, blk, lds, st>>>(a, rpg, row_groups, Kb);
     return hipGetLastError();
+}
+
+template <int N, int M, bool SMF>
+hipError_t launch_xlds_c(const SpmmArgs& a, hipStream_t st) {
+    if (a.act != nullptr) return launch_xlds_k<N, M, SMF, 4, false>(a, st);
+    if (a.ep_on && a.ep_res && a.y_bf16) return launch_xlds_k<N, M, SMF, 0, true>(a, st);
+    return launch_xlds_k<N, M, SMF, 0, false>(a, st);
 }
 
 template <int N, int M>
 hipError_t launch_xlds(const SpmmArgs& a, hipStream_t st) {
-    const bool strided = a.act != nullptr;
     if constexpr (smf_pattern<N, M>() || smf_flagged_pattern<N, M>()) {
-        if (smf_wanted<N, M>(a)) return strided ? launch_xlds_k<N, M, true, 4>(a, st) : launch_xlds_k<N, M, true, 0>(a, st);
+        if (smf_wanted<N, M>(a)) return launch_xlds_c<N, M, true>(a, st);
     }
-    return strided ? launch_xlds_k<N, M, false, 4>(a, st) : launch_xlds_k<N, M, false, 0>(a, st);
+    return launch_xlds_c<N, M, false>(a, st);
 }
 
 }  // namespace crisp

@@ -16,8 +16,9 @@ namespace crisp {
 constexpr int XRES_SHAPE = 20;          // launch shape code of this kernel for launch_reg_nm
 constexpr int XRES_MAX_GROUP = 32;      // block-rows per wave at most (their block list sits in one register per lane)
 
-// KB: block columns held (1 or 2).  rows_per_group: block-rows a wave walks.
-template <int N, int M, bool SMF, int KB>
+// KB: block columns held (1 or 2).  rows_per_group: block-rows a wave walks.  PRES: bf16 output with a residual
+// that is requested ahead across block-rows (ResidualStream).
+template <int N, int M, bool SMF, int KB, bool PRES>
 __global__ __launch_bounds__(256, 2) void spmm_xres_kernel(SpmmArgs p, int rows_per_group, int row_groups) {
     constexpr int B = 64;
     typedef Fmt<N, M, B> F;
@@ -139,6 +140,8 @@ __global__ __launch_bounds__(256, 2) void spmm_xres_kernel(SpmmArgs p, int rows_
     uint32_t av[RT][KS][F::VW], aw[RT][F::WPR];
     int t = t0;
     if (t0 <= t_last) Body::load_a(av, aw, p, a_off, i_off, t0);
+    ResidualStream<4> rs;
+    if constexpr (PRES) rs.start(p, bi0, bi1, hh, lane, col0, col_ok);
     for (int bi = bi0; bi < bi1; ++bi) {
         const int t_end = __builtin_amdgcn_readlane(my_ptr, bi + 1 - bi0);
 #pragma unroll
@@ -158,6 +161,10 @@ __global__ __launch_bounds__(256, 2) void spmm_xres_kernel(SpmmArgs p, int rows_
         int hh_now = hh;
         asm volatile("" : "+v"(hh_now));
         // eight rows at a time: the epilogue's operands of a batch of rows live beside the X operands
+        if constexpr (PRES) {
+            rs.store(p, bi, bi + 1, bi1, hh_now, lane, col0, col_ok, acc);
+            continue;
+        }
 #pragma unroll
         for (int r0 = 0; r0 < RT * 16; r0 += 8)
             store_rows<B, 1, 8, 1>(p, bi, hh_now, col0, col_ok, r0, [&](int pr, float (&v)[NACC]) __attribute__((always_inline)) {
@@ -173,7 +180,7 @@ inline bool xres_covers(const SpmmArgs& a, int B) {
            !(a.ep_on && a.ep_res && a.ep_ldr > ((int64_t)1 << 23));
 }
 
-template <int N, int M, bool SMF, int KB>
+template <int N, int M, bool SMF, int KB, bool PRES>
 hipError_t launch_xres_k(const SpmmArgs& a, hipStream_t st) {
     const int64_t strips = (a.Ncol + 255) / 256;
     // all block-rows in one group unless that leaves the chip short of workgroups
@@ -184,18 +191,26 @@ hipError_t launch_xres_k(const SpmmArgs& a, hipStream_t st) {
     if (wgs > INT32_MAX) return hipErrorInvalidValue;
     const dim3 grd((unsigned)wgs), blk(256);
     if (a.ev_start || a.ev_stop)
-        hipExtLaunchKernelGGL((spmm_xres_kernel<N, M, SMF, KB>), grd, blk, 0, st, a.ev_start, a.ev_stop, 0, a, rpg, row_groups);
+        hipExtLaunchKernelGGL((spmm_xres_kernel<N, M, SMF, KB, PRES>), grd, blk, 0, st, a.ev_start, a.ev_stop, 0, a, rpg, row_groups);
     else
-        spmm_xres_kernel<N, M, SMF, KB><<<grd, blk, 0, st>>>(a, rpg, row_groups);
+        spmm_xres_kernel<N, M, SMF, KB, PRES><<<grd, blk, 0, st>>>(a, rpg, row_groups);
     return hipGetLastError();
+}
+
+// One block column with a bf16 residual: the variant that requests the residual ahead.
+template <int N, int M, bool SMF>
+hipError_t launch_xres_kb(const SpmmArgs& a, hipStream_t st) {
+    if (a.K > 64) return launch_xres_k<N, M, SMF, 2, false>(a, st);
+    if (a.ep_on && a.ep_res && a.y_bf16) return launch_xres_k<N, M, SMF, 1, true>(a, st);
+    return launch_xres_k<N, M, SMF, 1, false>(a, st);
 }
 
 template <int N, int M>
 hipError_t launch_xres(const SpmmArgs& a, hipStream_t st) {
     if constexpr (smf_pattern<N, M>() || smf_flagged_pattern<N, M>()) {
-        if (smf_wanted<N, M>(a)) return a.K <= 64 ? launch_xres_k<N, M, true, 1>(a, st) : launch_xres_k<N, M, true, 2>(a, st);
+        if (smf_wanted<N, M>(a)) return launch_xres_kb<N, M, true>(a, st);
     }
-    return a.K <= 64 ? launch_xres_k<N, M, false, 1>(a, st) : launch_xres_k<N, M, false, 2>(a, st);
+    return launch_xres_kb<N, M, false>(a, st);
 }
 
 }  // namespace crisp
