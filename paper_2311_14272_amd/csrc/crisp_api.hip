@@ -491,7 +491,7 @@ static crisp_status conv_plan_impl(const crisp_layer_desc* desc, const crisp_con
         const bool strided_1x1 = conv->kh == 1 && conv->kw == 1 && conv->stride == 2 && conv->pad == 0 && (conv->W & 1) == 0 &&
                                  (Wo & 1) == 0 && aligned;
         if ((strided_1x1 && gathers <= STRIDED_1X1_MAX_GATHER) || paired || xlds_conv_would_run(*g, *conv, Ncol) ||
-            conv_lds_would_run(*g, desc->block_density, *conv, Ncol) ||
+            conv_lds_suits(*g, desc->block_density, *conv, Ncol) ||
             (conv->kh * conv->kw > 1 && gathers <= FUSED_GENERAL_MAX_GATHER)) {
             *path = CRISP_CONV_FUSED;
             return CRISP_OK;

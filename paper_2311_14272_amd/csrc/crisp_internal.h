@@ -47,7 +47,7 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
                        int x_layout = CRISP_X_KN);
 
 // Whether launch_spmm would run this convolution with the input patch staged in LDS (host only).
-bool conv_lds_would_run(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol);
+bool conv_lds_suits(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol);
 bool xlds_conv_would_run(const Geometry& g, const crisp_conv_desc& conv, int64_t Ncol);
 
 #define CRISP_BUDGET_MAX_LAYERS 64

@@ -409,18 +409,32 @@ template <> hipError_t launch_conv_lds_nm<8, 8>(const SpmmArgs&, const ConvLdsSc
 // waves split each block-row's list so that enough loads are in flight to cover the latency.
 static int pick_shape(const Geometry& g, int64_t Ncol, int blocks_per_row, bool smf);
 
-// Whether the LDS-staged convolution is the faster choice (measured on 3x3 layers of the ResNet-50
-// shapes, all patterns, block densities 0.25 .. 1): with at least half of the blocks kept the patch
+// Whether the LDS-staged convolution is the faster choice once the chip is full (measured on 3x3 layers of the
+// ResNet-50 shapes, all patterns, block densities 0.25 .. 1): with at least half of the blocks kept the patch
 // is reused often enough in every shape (1.1-1.4x over the register kernels); below that only where
 // a staged patch still serves about six kept blocks, the tiles are small (output width <= 28) and
 // one group of block-rows covers the layer (1.1-1.7x there, 0.7-0.9x elsewhere), and the grid
-// gives every compute unit a workgroup.
-static bool conv_lds_pays(const ConvLdsSched& s, int Sb, double density, int batch, int Wo) {
+// gives every compute unit a workgroup.  The choice between the fused lowering and a materialised X is made on this
+// alone: how the fused lowering is launched never decides whether a convolution needs scratch.
+static bool conv_lds_reuses(const ConvLdsSched& s, int Sb, double density, int batch, int Wo) {
     if (s.taps <= 1 || Sb < 2 || !(density <= 1.0)) return false;
     if (density >= 0.5) return true;
     const double blocks_per_patch = s.RG * density * s.taps;
     const int64_t wgs = (int64_t)batch * s.tiles_per_img * s.row_groups;
     return blocks_per_patch >= 6.0 && Sb <= 4 && Wo <= 28 && wgs >= 256;
+}
+
+// And whether it is launched: its waves keep one tile for all kept blocks, so few workgroups leave compute units
+// idle for that long, while the register kernels can split a tile's block list over four waves.  Measured on 3x3
+// layers of 128 to 512 channels at 14x14 ... 56x56, batch 1 to 256, 1:8, 2:4, 4:8 and 3:4, time over that of the
+// best register shape.  Stride 1: density 0.6, up to 64 workgroups 2.2-3.6 (256 channels, 14x14, batch 8: 24.4
+// against 9.8 us), 112-128 1.5-2.2, 224-256 0.95-1.4, 448-512 0.64-1.05; density 0.3, 256 1.2-1.6, 448 1.0-1.3,
+// 896 0.86-1.1.  Stride 2, where the register kernels fetch every element by itself: density 0.6, 32 workgroups
+// 1.9-2.4, 128 1.0-1.4, 512 0.41-0.59; density 0.3, 128 1.6-2.2, 512 0.68-0.88.
+static bool conv_lds_pays(const ConvLdsSched& s, int Sb, double density, int batch, int Wo, int stride) {
+    const int64_t wgs = (int64_t)batch * s.tiles_per_img * s.row_groups;
+    const int64_t least = stride == 1 ? (density >= 0.5 ? 384 : 640) : (density >= 0.5 ? 192 : 256);
+    return conv_lds_reuses(s, Sb, density, batch, Wo) && wgs >= least;
 }
 
 static int pick_shape(const Geometry& g, int64_t Ncol, int blocks_per_row, bool smf) {
@@ -432,9 +446,12 @@ static int pick_shape(const Geometry& g, int64_t Ncol, int blocks_per_row, bool 
         const bool heavy = 8 * g.n / g.m >= 4;   // 2:4
         if (blocks_per_row <= 2) return wide >= 2048 ? 0 : 1;
         if (narrow >= 1024) return ((!heavy && blocks_per_row >= 7) || blocks_per_row >= 20) ? 0 : 1;
-        // few tiles and long rows: four waves split a tile's block list (32x32 blocks only when the tiles
-        // are very few: c1 with 392 tiles 9.5 vs 11.7 us, c4a with 490 tiles 14.7 vs 12.2 us)
-        return (blocks_per_row >= 8 && (g.B == 64 || narrow < 448)) ? 2 : 1;
+        // few tiles: four waves split a tile's block list.  Below 448 tiles from 192 columns of kept blocks on
+        // (64x64 blocks, 3 / 5 / 11 blocks per row: 4.0 / 4.9 / 6.2 against 5.4 / 8.0 / 14.0 us with 4 to 196
+        // tiles, 5.0 / 6.6 / 9.5 against 5.9 / 8.9 / 14.8 us with 392), above only long rows (784 tiles: 8.0 / 10.9
+        // / 15.0 against 6.4 / 9.8 / 15.5 us; 32x32 blocks with 490 tiles 14.7 against 12.2 us)
+        if (narrow < 448) return blocks_per_row * g.B >= 192 ? 2 : 1;
+        return (blocks_per_row >= 8 && g.B == 64) ? 2 : 1;
     }
     // 4:8 expands through a selector table (a handful of instructions per operand): as with the sparse
     // instruction there is little to share between columns, and narrow strips win from two blocks per row on
@@ -522,16 +539,16 @@ bool xlds_conv_would_run(const Geometry& g, const crisp_conv_desc& conv, int64_t
            ((sparse_ok && xlds_pays(g.Sb, g.Kb, Ncol, true)) || (dense48 && xlds_pays(g.Sb, g.Kb, Ncol, false)));
 }
 
-// Whether launch_spmm, left to its own choice, runs this convolution in the kernel that stages the
-// input patch in LDS (the callers that choose between the fused lowering and a materialised X ask).
-bool conv_lds_would_run(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol) {
+// Whether the kernel that stages the input patch in LDS suits this convolution (the callers that choose between the
+// fused lowering and a materialised X ask; with too few workgroups the register kernels run the fused lowering).
+bool conv_lds_suits(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol) {
     if (g.B == 16) return false;
     SpmmArgs a = {};
     a.S = g.S; a.K = g.K; a.Sb = g.Sb; a.Ncol = Ncol;
     a.act = reinterpret_cast<const uint16_t*>(&a);      // any non-null value: never dereferenced on the host
     fill_conv_args(a, g, conv);
     ConvLdsSched cs;
-    return (Ncol % 4) == 0 && conv_lds_plan(a, g.B, conv.kh, &cs) && conv_lds_pays(cs, g.Sb, density_hint, conv.batch, a.Wo);
+    return (Ncol % 4) == 0 && conv_lds_plan(a, g.B, conv.kh, &cs) && conv_lds_reuses(cs, g.Sb, density_hint, conv.batch, a.Wo);
 }
 
 hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows, int force_shape, const int32_t* row_ptr,
@@ -588,7 +605,7 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
     ConvLdsSched cs;
     const bool conv_lds_wanted = force_shape == 12 || force_shape < 0;
     if (conv && conv_lds_wanted && (Ncol % 4) == 0 && ld_wide <= ((int64_t)1 << 23) && conv_lds_plan(a, g.B, conv->kh, &cs) &&
-        (force_shape == 12 || conv_lds_pays(cs, g.Sb, density_hint, conv->batch, a.Wo))) {
+        (force_shape == 12 || conv_lds_pays(cs, g.Sb, density_hint, conv->batch, a.Wo, a.stride))) {
         a.use_smf = 1;
         report(CRISP_KERNEL_CONV_LDS, 0, a.conv_mode, g.n <= 2);
         switch (g.n * 16 + g.m) {
