@@ -748,6 +748,34 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
         }
         if (conv) return hipErrorInvalidValue;  // callers check the pattern first
     }
+    // Plain X whose K is no multiple of 16 or whose Ncol is none of 4: the register kernels with ranged resources
+    // (narrow strips, or the split by four).  Against the generic kernel, bf16 output, densities 0.3 and 0.7, 1:8, 2:4,
+    // 4:8 and 3:4: 64x64 blocks 1.24-5.0x (512 x 2305 x 50003 2:4 276 -> 130 us at 0.3; 256 x 1153 x 197 59 -> 12 us at
+    // 0.7), 32x32 blocks 1.02-4.0x -- but 0.87-0.98x for patterns of the sparse instruction with ten or more blocks per
+    // row under at most 16 block-rows and many tiles (512 x 2305 x 50003 1:8 at 0.7: 364 against 419 us), where the
+    // generic kernel's wide strips fetch a block's slices once for 512 columns; there it stays.
+    const bool long_b32 = g.B == 32 && g.n <= 2 && bpr >= 10 && g.Sb <= 16 && (int64_t)g.Sb * ((Ncol + 63) / 64) >= 1024;
+    if (!conv && force_shape < 0 && !long_b32 && ld_wide <= ((int64_t)1 << 23) && ldx <= ((int64_t)1 << 23)) {
+        a.ragged = 1;
+        a.use_smf = 1;
+        const int shape_r = shape <= 1 ? 1 : 2;
+        auto run = [&](auto launch) {
+            report(CRISP_KERNEL_REG, shape_r, 0, smf_ok);
+            return launch();
+        };
+        switch (g.n * 16 + g.m) {
+            case 1 * 16 + 4: return run([&] { return launch_reg_nm<1, 4>(a, g.B, shape_r, st); });
+            case 2 * 16 + 4: return run([&] { return launch_reg_nm<2, 4>(a, g.B, shape_r, st); });
+            case 3 * 16 + 4: return run([&] { return launch_reg_nm<3, 4>(a, g.B, shape_r, st); });
+            case 4 * 16 + 4: return run([&] { return launch_reg_nm<4, 4>(a, g.B, shape_r, st); });
+            case 1 * 16 + 8: return run([&] { return launch_reg_nm<1, 8>(a, g.B, shape_r, st); });
+            case 2 * 16 + 8: return run([&] { return launch_reg_nm<2, 8>(a, g.B, shape_r, st); });
+            case 4 * 16 + 8: return run([&] { return launch_reg_nm<4, 8>(a, g.B, shape_r, st); });
+            case 8 * 16 + 8: return run([&] { return launch_reg_nm<8, 8>(a, g.B, shape_r, st); });
+            default: break;
+        }
+        a.ragged = 0;
+    }
     // any other n:m (or forced): the generic LDS-expansion kernel
     const bool wide = (int64_t)g.Sb * ((Ncol + 511) / 512) >= 512;
     report(CRISP_KERNEL_GENERIC, wide, 0, 0);

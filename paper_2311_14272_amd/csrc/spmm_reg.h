@@ -12,8 +12,9 @@
 //     v_mfma_f32_32x32x16_bf16 -- or, for patterns with at most two kept per group (SMF), handed
 //     almost unchanged to the sparse matrix-core instruction v_smfmac_f32_32x32x32_bf16;
 //   * accumulation in fp32.
-// With CONV != 0 the X rows are not read from a materialised matrix but located inside the
-// convolution's input (three modes, see SpmmArgs).
+// With CONV 1 to 4 the X rows are not read from a materialised matrix but located inside the
+// convolution's input (see SpmmArgs); CONV 6 is plain X with any K and Ncol (rows past K read as zero
+// through the resource's range, columns past Ncol are left out when Y is stored).
 // Nothing goes through LDS in the loop and waves never wait for each other, so every wave keeps
 // PF blocks of X in flight.  Two ways to spread work:
 //   NWK == 1: the 4 waves of a workgroup own 4 neighbouring column strips (large Ncol);
@@ -72,6 +73,7 @@ struct SpmmArgs {
     const void* ep_res;       // S x ep_ldr, same element type as Y
     int64_t ep_ldr;
     int use_smf;              // host side only: sparse-MFMA instantiation wanted (eligible patterns)
+    int ragged;               // host side only: K % 16 or Ncol % 4 is not 0 (plain X; CONV == 6 instantiations)
     int two_of_four;          // host side only: 4:8 pack with at most two values per aligned four (caller's assertion)
     // host side only: optional events that receive the kernel's own start and stop time stamps
     hipEvent_t ev_start, ev_stop;
@@ -601,6 +603,15 @@ struct BlockBody {
                 const uint32_t e1 = __builtin_amdgcn_raw_buffer_load_b16(r, o1, 0, 0);
                 dst[i] = u32x2{e0, e1};
             }
+        } else if constexpr (CONV == 6) {
+            // plain X with any K: the resource ends with the last row, so rows past it read as zero (the row is part
+            // of the lane offset, which is what the range check looks at)
+            const int kb = bj * B + ks * 16;
+            const uint32_t row_bytes = (uint32_t)p.ldx * 2u;
+            const rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.X + (int64_t)kb * p.ldx), 0,
+                                                               (uint32_t)min(max(p.K - kb, 0), 16) * row_bytes, 0x00020000);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) dst[i] = buf_load_x<WD>(r, lane_off + (uint32_t)i * row_bytes, 0);
         } else if constexpr (CONV != 0) {
             // K-row = tap*C + c: the 16 rows of the step are 16 consecutive channel planes
             const int tap = (int)(((float)bj + 0.5f) * p.inv_cpb);
@@ -683,14 +694,14 @@ struct BlockBody {
                 if constexpr (CONV == 5) {
                     lo[q] = xd[q][0];           // loaded in operand form
                     hi[q] = xd[4 + q][0];
-                } else if constexpr (CONV >= 2) {
+                } else if constexpr (CONV >= 2 && CONV <= 4) {
                     // register 0 of a row holds the first column's element, register 1 the second's
                     lo[q] = __builtin_amdgcn_perm(xd[2 * q + 1][0], xd[2 * q][0], cur.sel_lo);
                     hi[q] = __builtin_amdgcn_perm(xd[2 * q + 1][1], xd[2 * q][1], cur.sel_hi);
                 } else {
                     const uint32_t r0 = xd[2 * q][pd], r1 = xd[2 * q + 1][pd];
-                    lo[q] = __builtin_amdgcn_perm(r1, r0, CONV ? cur.sel_lo : SEL_LO);  // first column of the pair
-                    hi[q] = __builtin_amdgcn_perm(r1, r0, CONV ? cur.sel_hi : SEL_HI);  // second column
+                    lo[q] = __builtin_amdgcn_perm(r1, r0, CONV == 1 ? cur.sel_lo : SEL_LO);  // first column of the pair
+                    hi[q] = __builtin_amdgcn_perm(r1, r0, CONV == 1 ? cur.sel_hi : SEL_HI);  // second column
                 }
             }
             bfrag[2 * pd] = __builtin_bit_cast(bf16x8, lo);
@@ -730,13 +741,13 @@ struct BlockBody {
                     if constexpr (CONV == 5) {
                         lo[q] = xd[q][0];
                         hi[q] = xd[4 + q][0];
-                    } else if constexpr (CONV >= 2) {
+                    } else if constexpr (CONV >= 2 && CONV <= 4) {
                         lo[q] = __builtin_amdgcn_perm(xd[2 * q + 1][0], xd[2 * q][0], cur.sel_lo);
                         hi[q] = __builtin_amdgcn_perm(xd[2 * q + 1][1], xd[2 * q][1], cur.sel_hi);
                     } else {
                         const uint32_t r0 = xd[2 * q][pd], r1 = xd[2 * q + 1][pd];
-                        lo[q] = __builtin_amdgcn_perm(r1, r0, CONV ? cur.sel_lo : SEL_LO);
-                        hi[q] = __builtin_amdgcn_perm(r1, r0, CONV ? cur.sel_hi : SEL_HI);
+                        lo[q] = __builtin_amdgcn_perm(r1, r0, CONV == 1 ? cur.sel_lo : SEL_LO);
+                        hi[q] = __builtin_amdgcn_perm(r1, r0, CONV == 1 ? cur.sel_hi : SEL_HI);
                     }
                 }
                 half[k2][2 * pd] = lo;
@@ -771,7 +782,7 @@ struct BlockBody {
         XCtx nx = cx;
         if constexpr (PREFETCH) {
             bj_next = bj_known >= 0 ? bj_known : p.col_idx[t_next];
-            if constexpr (CONV != 0 && CONV != 5) nx = conv_ctx(p, cp, bj_next);
+            if constexpr (CONV != 0 && CONV < 5) nx = conv_ctx(p, cp, bj_next);
         }
         // drop the other half-wave's position bits: bit 0 of ws is this lane's first slot
         uint32_t ws[RT][F::WPR];
@@ -810,7 +821,8 @@ struct BlockBody {
 // The four (epilogue yes/no) x (bf16/fp32 output) variants of the store loop are separate copies
 // chosen once per wave, so the loop itself holds no branches; with an epilogue its operands are
 // requested for a batch of rows before the first of them is used.
-template <int B, int WD, int ROWS, int ROW_STEP, typename RowSource>
+// RAGGED: any Ncol -- a lane whose columns straddle the last one stores those that exist one by one.
+template <int B, int WD, int ROWS, int ROW_STEP, bool RAGGED = false, class RowSource>
 __device__ __forceinline__ void store_rows(const SpmmArgs& p, int bi, int hh, int64_t col0, bool col_ok, int row_first,
                                            RowSource row_source) {
     constexpr int NACC = 2 * WD;
@@ -819,7 +831,10 @@ __device__ __forceinline__ void store_rows(const SpmmArgs& p, int bi, int hh, in
     const int rows_here = min(B, p.S - bi * B);
     const rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(
         reinterpret_cast<char*>(p.Y) + (int64_t)bi * B * p.ldy * esz, 0, (uint32_t)rows_here * row_bytes, 0x00020000);
-    const uint32_t y_off = col_ok ? (uint32_t)(4 * hh) * row_bytes + (uint32_t)col0 * esz : 0x80000000u;
+    const uint32_t y_lane = (uint32_t)(4 * hh) * row_bytes + (uint32_t)col0 * esz;
+    const bool straddles = RAGGED && col_ok && col0 + NACC > p.Ncol;
+    const bool any_straddles = RAGGED && __any(straddles);
+    const uint32_t y_off = (col_ok && !straddles) ? y_lane : 0x80000000u;
     auto tile_row_of = [&](int q) __attribute__((always_inline)) {
         const int pr = row_first + q * ROW_STEP;
         return (pr >> 4) * 32 + 8 * ((pr & 15) >> 2) + (pr & 3);
@@ -828,6 +843,21 @@ __device__ __forceinline__ void store_rows(const SpmmArgs& p, int bi, int hh, in
         constexpr bool BF16 = decltype(as_bf16)::value;
         auto store_row = [&](int tile_row, const float (&v)[NACC]) __attribute__((always_inline)) {
             const uint32_t off = y_off + (uint32_t)tile_row * row_bytes;
+            if constexpr (RAGGED) {
+                if (any_straddles) {
+#pragma unroll
+                    for (int c = 0; c + 1 < NACC; ++c) {
+                        const uint32_t one = (straddles && col0 + c < p.Ncol) ? y_lane + (uint32_t)c * esz + (uint32_t)tile_row * row_bytes : 0x80000000u;
+                        if constexpr (BF16) {
+                            const f32x2 two = {v[c], v[c]};
+                            __builtin_amdgcn_raw_buffer_store_b16(
+                                (unsigned short)(__builtin_bit_cast(uint32_t, __builtin_convertvector(two, bf16x2)) & 0xFFFFu), ry, one, 0, 0);
+                        } else {
+                            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[c]), ry, one, 0, 0);
+                        }
+                    }
+                }
+            }
             if constexpr (BF16) {
                 uint32_t pk[WD];
 #pragma unroll
@@ -978,7 +1008,7 @@ constexpr int waves_per_simd() { return (WD == 2 && B == 64 && Fmt<N, M, B>::FS 
 // (upper limit: three for the narrow-strip kernels of the sparse matrix-core patterns on plain X, whose
 // registers allow it)
 template <int N, int M, int B, int WD, int NWK, int CONV, bool SMF>
-constexpr int waves_per_simd_max() { return (WD == 1 && SMF && NWK == 1 && CONV == 0 && B == 64) ? 3 : 2; }
+constexpr int waves_per_simd_max() { return (WD == 1 && SMF && NWK == 1 && (CONV == 0 || CONV == 6) && B == 64) ? 3 : 2; }
 
 template <int N, int M, int B, int WD, int NWK, int PF, int CONV, bool SMF = false>
 __global__ __launch_bounds__(NWK > 1 ? 64 * NWK : 256)
@@ -1024,7 +1054,8 @@ void spmm_reg_kernel(SpmmArgs p) {
     const int64_t col_ld = col_ok ? col0 : 0;
     ConvPos cp = {0, 0, 0, 0u, 0, 0, 0, lut48};
     uint32_t lane_off = 0;
-    if constexpr (CONV != 0) {
+    constexpr bool LOWERED = CONV != 0 && CONV != 6;
+    if constexpr (LOWERED) {
         // column -> (image, oh, ow); exact division through fp64 reciprocals (col < 2^31)
         const int j = (int)col_ld;
         int t = (int)((double)j * p.inv_Wo);
@@ -1074,7 +1105,7 @@ void spmm_reg_kernel(SpmmArgs p) {
         if (d < cnt) {
             const int t = first + d * NWK;
             const int bj = p.col_idx[t];
-            if constexpr (CONV != 0) cx[d] = BodyL::conv_ctx(p, cp, bj);
+            if constexpr (LOWERED) cx[d] = BodyL::conv_ctx(p, cp, bj);
             else cx[d] = XCtx{lane_off, SEL_LO, SEL_HI, 0u};
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) BodyL::load_x(xr[d][ks], p, cp, cx[d].off, cx[d].off2, bj, ks);
@@ -1104,7 +1135,7 @@ void spmm_reg_kernel(SpmmArgs p) {
 
     // ---- epilogue ---------------------------------------------------------------------------
     if constexpr (NWK == 1) {
-        store_rows<B, WD, RT * 16, 1>(p, bi, hh, col0, col_ok, 0, [&](int pr, float (&v)[NACC]) __attribute__((always_inline)) {
+        store_rows<B, WD, RT * 16, 1, CONV == 6>(p, bi, hh, col0, col_ok, 0, [&](int pr, float (&v)[NACC]) __attribute__((always_inline)) {
 #pragma unroll
             for (int c = 0; c < NACC; ++c) v[c] = acc[pr >> 4][c][pr & 15];
         });
@@ -1118,7 +1149,7 @@ void spmm_reg_kernel(SpmmArgs p) {
 #pragma unroll
                 for (int c = 0; c < NACC; ++c) red[wave][rt * 16 + r][c][lane] = acc[rt][c][r];
         __syncthreads();
-        store_rows<B, WD, RT * 16 / NWK, NWK>(p, bi, hh, col0, col_ok, wave, [&](int pr, float (&v)[NACC]) __attribute__((always_inline)) {
+        store_rows<B, WD, RT * 16 / NWK, NWK, CONV == 6>(p, bi, hh, col0, col_ok, wave, [&](int pr, float (&v)[NACC]) __attribute__((always_inline)) {
 #pragma unroll
             for (int c = 0; c < NACC; ++c) {
                 float s = red[0][pr][c][lane];
@@ -1148,7 +1179,7 @@ hipError_t launch_reg_k(const SpmmArgs& a, hipStream_t st) {
 
 template <int N, int M, int B, int WD, int NWK, int PF, int CONV>
 hipError_t launch_reg(const SpmmArgs& a, hipStream_t st) {
-    if constexpr (smf_pattern<N, M>() || (smf_flagged_pattern<N, M>() && CONV == 0)) {
+    if constexpr (smf_pattern<N, M>() || (smf_flagged_pattern<N, M>() && (CONV == 0 || CONV == 6))) {
         if (smf_wanted<N, M>(a)) return launch_reg_k<N, M, B, WD, NWK, PF, CONV, true>(a, st);
     }
     return launch_reg_k<N, M, B, WD, NWK, PF, CONV, false>(a, st);
@@ -1190,6 +1221,7 @@ hipError_t launch_reg_shape(const SpmmArgs& a, int shape, hipStream_t st) {
             default: return launch_reg<N, M, B, 1, 8, 1, 1>(a, st);
         }
     }
+    if (a.ragged) return shape <= 1 ? launch_reg<N, M, B, 1, 1, 1, 6>(a, st) : launch_reg<N, M, B, 1, 4, 1, 6>(a, st);
     switch (shape) {
         case 0: return launch_reg<N, M, B, 2, 1, 1, 0>(a, st);
         case 1: return launch_reg<N, M, B, 1, 1, 1, 0>(a, st);

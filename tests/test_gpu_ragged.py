@@ -1,0 +1,51 @@
+"""Products whose K is no multiple of 16 or whose column count is none of 4: the register kernels with ranged resources
+(the automatic choice) against the generic kernel (forced shape 4).  X carries NaN past its last row and column, Y a
+guard band, so that a read or write past the edges shows."""
+import pytest
+import torch
+
+from paper_2311_14272_amd import crisp
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,m", [(1, 4), (2, 4), (3, 4), (4, 4), (1, 8), (2, 8), (4, 8), (8, 8)])
+@pytest.mark.parametrize("B", [32, 64])
+@pytest.mark.parametrize("S,K,N", [(5, 9, 1), (64, 16, 3), (203, 459, 66), (70, 147, 131), (130, 1000, 1), (33, 1001, 257),
+                                   (96, 640, 2049), (2100, 72, 510)])
+@pytest.mark.parametrize("ep,topk", [(0, 0), (1, 0), (1, 1)])
+def test_ragged_product(n, m, B, S, K, N, ep, topk):
+    g = torch.Generator(device="cuda").manual_seed(S + K + N)
+    mode = crisp.LAYER_TOPK if topk else crisp.ROW_UNIFORM
+    layer = crisp.alloc_layer(crisp.layer_desc(S, K, n, m, B, 0.6, crisp.SAL_MAG, mode))
+    W = (torch.randn((S, K), generator=g, device="cuda") * 0.1).to(torch.bfloat16).view(torch.int16)
+    crisp.prune_and_pack(layer, W, None)
+    ld = (N + 7) // 8 * 8
+    Xf = torch.full((K + 80, ld), float("nan"), dtype=torch.bfloat16, device="cuda")
+    Xf[:K, :N] = torch.randn((K, N), generator=g, device="cuda").to(torch.bfloat16)
+    X = Xf.view(torch.int16)
+    sc = torch.rand(S, generator=g, device="cuda") + 0.5
+    bs = torch.randn(S, generator=g, device="cuda")
+    res = torch.full((S, ld + 8), float("nan"), dtype=torch.bfloat16, device="cuda")
+    res[:, :N] = torch.randn((S, N), generator=g, device="cuda").to(torch.bfloat16)
+
+    def product(dtype, shape):
+        Y = torch.full((S + 1, ld), 7.0, dtype=dtype, device="cuda")
+        r = res.to(dtype)
+        e = crisp.epilogue(sc, bs, r, ld + 8, True) if ep else None
+        code = crisp.crisp_spmm_forced(layer.desc, layer.row_ptr, layer.col_idx, layer.vals, layer.idx_words, X, N, ld, Y, ld,
+                                       crisp.Y_BF16 if dtype == torch.bfloat16 else crisp.Y_F32, e, shape)
+        torch.cuda.synchronize()
+        assert bool((Y[S] == 7.0).all()) and bool((Y[:S, N:] == 7.0).all()), "guard band written"
+        return Y[:S, :N], crisp.kernel_code_fields(code)["family"]
+
+    ref, family = product(torch.float32, 4)
+    assert family == "generic"
+    y, family = product(torch.float32, crisp.SHAPE_AUTO)
+    if K % 16 or N % 4:
+        assert family == "reg"
+    # the products are exact in fp32 and only their order differs: at most K roundings of 2^-24 of the sum of the
+    # magnitudes, which the values here keep under 0.1 * K, plus those of the tail (outputs of about ten at most)
+    assert float((y - ref).abs().max()) <= 2.0 ** -24 * (K * 0.1 * K * 0.6 + 64)
+    yb, _ = product(torch.bfloat16, crisp.SHAPE_AUTO)
+    assert torch.equal(y.to(torch.bfloat16), yb)
