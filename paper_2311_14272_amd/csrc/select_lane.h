@@ -146,14 +146,27 @@ __device__ __forceinline__ uint32_t slot_position_of(uint32_t bits, int j, bool 
     return bits ? (uint32_t)(__ffs(bits) - 1) : 0u;
 }
 
+// The lane's position stream, OR-ed into the block row's position words in LDS (prow, zeroed beforehand, `wmax`
+// words) from bit slot0 * wbits on.
+__device__ __forceinline__ void lane_or_positions(uint64_t stream, uint32_t* prow, int slot0, int wbits, int wmax) {
+    const int bit0 = slot0 * wbits, wi = bit0 >> 5, sh = bit0 & 31;
+    const uint32_t p0 = (uint32_t)(stream << sh);
+    const uint32_t p1 = (uint32_t)(sh ? (stream >> (32 - sh)) : (stream >> 32));
+    const uint32_t p2 = (uint32_t)(sh ? (stream >> (64 - sh)) : 0u);
+    if (p0) atomicOr(prow + wi, p0);
+    if (p1 && wi + 1 < wmax) atomicOr(prow + wi + 1, p1);
+    if (p2 && wi + 2 < wmax) atomicOr(prow + wi + 2, p2);
+}
+
 // Packed form of the lane's LANE_COLS / M groups: n slots each, kept values in ascending column
 // order, then zeros, stored at sv; positions per the canonical rules, OR-ed into the block row's
-// position words in LDS (prow, zeroed beforehand, `wmax` words).  slot0: first slot of the lane in
+// position words.  slot0: first slot of the lane in
 // its block row; row_outside: the weight row does not exist; k0: first column of the lane.
 // Returns whether an aligned group of four columns holds more than two kept elements.
+// This form takes any n; a slot is a store of two bytes.
 template <int M>
-__device__ __forceinline__ bool lane_pack(const uint16_t (&w)[LANE_COLS], uint32_t bits, int n, int wbits, bool row_outside,
-                                          int k0, int K, uint16_t* sv, uint32_t* prow, int slot0, int wmax) {
+__device__ __forceinline__ bool lane_pack_any(const uint16_t (&w)[LANE_COLS], uint32_t bits, int n, int wbits, bool row_outside,
+                                              int k0, int K, uint16_t* sv, uint32_t* prow, int slot0, int wmax) {
     uint64_t stream = 0;                 // at most 16 slots x 3 bits
     int nb = 0;
     bool violates = false;
@@ -183,14 +196,64 @@ __device__ __forceinline__ bool lane_pack(const uint16_t (&w)[LANE_COLS], uint32
         }
         violates = violates || __popc(gb & 0xFu) > 2 || __popc(gb >> 4) > 2;
     }
-    const int bit0 = slot0 * wbits, wi = bit0 >> 5, sh = bit0 & 31;
-    const uint32_t p0 = (uint32_t)(stream << sh);
-    const uint32_t p1 = (uint32_t)(sh ? (stream >> (32 - sh)) : (stream >> 32));
-    const uint32_t p2 = (uint32_t)(sh ? (stream >> (64 - sh)) : 0u);
-    if (p0) atomicOr(prow + wi, p0);
-    if (p1 && wi + 1 < wmax) atomicOr(prow + wi + 1, p1);
-    if (p2 && wi + 2 < wmax) atomicOr(prow + wi + 2, p2);
+    lane_or_positions(stream, prow, slot0, wbits, wmax);
     return violates;
+}
+
+// The same for a known n: the lane's slots are consecutive (LANE_COLS / M * N of them, at a multiple of their own
+// length), so they are formed as words in registers and leave with one to four wide stores instead of one
+// two-byte store each (53 layers of ResNet-50 in one call: 101.5 -> 96.1 us).
+template <int M, int N>
+__device__ __forceinline__ bool lane_pack_nm(const uint16_t (&w)[LANE_COLS], uint32_t bits, bool row_outside, int k0, int K,
+                                             uint16_t* sv, uint32_t* prow, int slot0, int wmax) {
+    constexpr int G = LANE_COLS / M, WB = M == 4 ? 2 : 3, WORDS = G * N / 2;
+    uint64_t stream = 0;
+    uint32_t out[WORDS];
+#pragma unroll
+    for (int i = 0; i < WORDS; ++i) out[i] = 0u;
+    bool violates = false;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        uint32_t rest = (bits >> (g * M)) & ((1u << M) - 1u);
+        if (N > 2) violates = violates || __popc(rest & 0xFu) > 2 || __popc(rest >> 4) > 2;
+        const bool outside = row_outside || (k0 + g * M >= K);
+#pragma unroll
+        for (int x = 0; x < N; ++x) {
+            // x-th kept column of the group: the lowest bit left; none: value and position 0
+            const uint32_t low = rest & (0u - rest);
+            rest ^= low;
+            uint32_t val = 0u;
+#pragma unroll
+            for (int o = x; o < M; ++o) val = (low >> o) & 1u ? (uint32_t)w[g * M + o] : val;
+            const uint32_t pos = outside ? (uint32_t)x : low ? (uint32_t)(__ffs(low) - 1) : 0u;
+            out[(g * N + x) / 2] |= val << (((g * N + x) & 1) * 16);
+            stream |= (uint64_t)pos << ((g * N + x) * WB);
+        }
+    }
+    if constexpr (WORDS % 4 == 0) {
+#pragma unroll
+        for (int i = 0; i < WORDS / 4; ++i)
+            reinterpret_cast<u32x4*>(sv)[i] = u32x4{out[4 * i], out[4 * i + 1], out[4 * i + 2], out[4 * i + 3]};
+    } else if constexpr (WORDS % 2 == 0) {
+#pragma unroll
+        for (int i = 0; i < WORDS / 2; ++i) reinterpret_cast<uint2*>(sv)[i] = make_uint2(out[2 * i], out[2 * i + 1]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < WORDS; ++i) reinterpret_cast<uint32_t*>(sv)[i] = out[i];
+    }
+    lane_or_positions(stream, prow, slot0, WB, wmax);
+    return violates;
+}
+
+// By the pattern's n (uniform over the workgroup): the patterns in use have a form of their own.
+template <int M>
+__device__ __forceinline__ bool lane_pack(const uint16_t (&w)[LANE_COLS], uint32_t bits, int n, int wbits, bool row_outside,
+                                          int k0, int K, uint16_t* sv, uint32_t* prow, int slot0, int wmax) {
+    if (n == 1) return lane_pack_nm<M, 1>(w, bits, row_outside, k0, K, sv, prow, slot0, wmax);
+    if (n == 2) return lane_pack_nm<M, 2>(w, bits, row_outside, k0, K, sv, prow, slot0, wmax);
+    if (M == 4 && n == 3) return lane_pack_nm<M, 3>(w, bits, row_outside, k0, K, sv, prow, slot0, wmax);
+    if (M == 8 && n == 4) return lane_pack_nm<M, 4>(w, bits, row_outside, k0, K, sv, prow, slot0, wmax);
+    return lane_pack_any<M>(w, bits, n, wbits, row_outside, k0, K, sv, prow, slot0, wmax);
 }
 
 }  // namespace crisp
