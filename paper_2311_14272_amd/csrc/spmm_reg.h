@@ -1209,8 +1209,9 @@ hipError_t launch_reg_shape(const SpmmArgs& a, int shape, hipStream_t st) {
         switch (shape) {
             case 0:
             case 1: return launch_reg<N, M, B, 1, 1, 1, 2>(a, st);
-            case 2: return launch_reg<N, M, B, 1, 4, 1, 2>(a, st);
-            default: return launch_reg<N, M, B, 1, 8, 1, 2>(a, st);
+            // (no split by eight: that instantiation, 2:4 in dense expansion, gave a wrong product in two of four
+            // runs of the random convolutions, cause not found)
+            default: return launch_reg<N, M, B, 1, 4, 1, 2>(a, st);
         }
     }
     if (a.act != nullptr) {
