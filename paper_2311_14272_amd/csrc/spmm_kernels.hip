@@ -732,7 +732,7 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
         const bool known = key == 0x14 || key == 0x24 || key == 0x34 || key == 0x44 || key == 0x18 || key == 0x28 ||
                            key == 0x48 || key == 0x88;
         // (the fused lowering has the narrow shapes only)
-        const int shape_run = (xres || xlds) ? 0 : (conv && shape == 0) ? 1 : (conv && a.conv_mode == 2 && shape == 3) ? 2 : shape;
+        const int shape_run = (xres || xlds) ? 0 : (conv && shape == 0) ? 1 : shape;
         if (known) report(xres ? CRISP_KERNEL_XRES : xlds ? CRISP_KERNEL_XLDS : CRISP_KERNEL_REG, shape_run, conv ? a.conv_mode : 0,
                           a.use_smf && (g.n <= 2 || (g.two_of_four && (!conv || xlds))));
         switch (key) {

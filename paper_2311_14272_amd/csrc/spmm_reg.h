@@ -1033,10 +1033,12 @@ void spmm_reg_kernel(SpmmArgs p) {
     if (nt >= p.NT) return;
 
     const int tid = threadIdx.x, lane = tid & 63;
-    // (uniform by construction and said so: with NWK > 1 the wave's blocks depend on it, and block numbers in
-    // vector registers turn every request's scalar base and offset into a loop over the lanes' values; 256 x 1152
-    // x 3136 2:4 with 32 x 32 blocks: 9.1 -> 7.9 us)
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // (uniform by construction and said so up to four waves: with the list split, the wave's blocks depend on it,
+    // and block numbers in vector registers turn every request's scalar base and offset into a loop over the lanes'
+    // values; 256 x 1152 x 3136 2:4 with 32 x 32 blocks: 9.1 -> 7.9 us.  Not in the split by eight: with uniform
+    // block numbers that one gave a wrong product, now and then, for a strided 2:4 convolution in dense expansion,
+    // and reading showed no cause; without them it never did.)
+    const int wave = NWK > 4 ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6);
     const int jj = lane & 31, hh = lane >> 5;
     // selector table of the dense 4:8 expansion, built by the whole workgroup before any wave leaves
     constexpr bool LUT48 = lut48_pattern<N, M, SMF>();
@@ -1209,9 +1211,8 @@ hipError_t launch_reg_shape(const SpmmArgs& a, int shape, hipStream_t st) {
         switch (shape) {
             case 0:
             case 1: return launch_reg<N, M, B, 1, 1, 1, 2>(a, st);
-            // (no split by eight: that instantiation, 2:4 in dense expansion, gave a wrong product in two of four
-            // runs of the random convolutions, cause not found)
-            default: return launch_reg<N, M, B, 1, 4, 1, 2>(a, st);
+            case 2: return launch_reg<N, M, B, 1, 4, 1, 2>(a, st);
+            default: return launch_reg<N, M, B, 1, 8, 1, 2>(a, st);
         }
     }
     if (a.act != nullptr) {

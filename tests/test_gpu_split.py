@@ -1,0 +1,48 @@
+"""The kernels in which four or eight waves split a tile's block list: a strided convolution with long block lists, in
+every split, against the oracle and bit for bit against the explicit lowering in the same launch shape, with the input
+at another address in every launch."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2311_14272_amd import crisp, synth
+
+from gpu_util import check_product, dev, run_select_pack, run_spmm
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,m,B", [(2, 4, 64), (3, 4, 64), (1, 8, 32)])
+@pytest.mark.parametrize("geom", [(128, 22, 41, 4, 7, 2, 3), (64, 9, 20, 2, 3, 2, 1)])
+def test_split_repeats_itself(n, m, B, geom):
+    C_, H, W_, b, k, stride, pad = geom
+    cv = synth.ConvShape(C_, H, W_, b, k, k, stride, pad)
+    L = synth.LayerSpec("split", 64, cv.K, cv.Ncol, n, m, B, 0.5, synth.SAL_MAG, 0.05, conv=cv)
+    rng = np.random.default_rng(n * 100 + m + C_)
+    W, act = synth.draw_weight(rng, L), synth.draw_relu_normal(rng, (C_, b, H, W_))
+    sel = oracle.select(W, None, n, m, B, 0.5, synth.SAL_MAG, L.select_mode)
+    X = oracle.im2col(act, k, k, stride, pad)
+    Yref, Aref = oracle.gemm_masked(W, sel.mask, X)
+    layer, _ = run_select_pack(L, W, None)
+    conv, Ncol, ld = crisp.conv_desc_of(cv), cv.Ncol, (cv.Ncol + 7) // 8 * 8
+    dact = dev(act).reshape(-1)
+    pool = torch.empty(8 * (dact.numel() + 64), dtype=torch.int16, device="cuda")
+    Xp = np.zeros((cv.K, ld), dtype=np.uint16)
+    Xp[:, :Ncol] = X
+    dX = dev(Xp)
+    for shape, split in ((2, 2), (3, 3), (9, 2), (10, 3)):
+        explicit = run_spmm(layer, dX, Ncol, ld, crisp.Y_F32, L.S, shape=shape)
+        check_product(explicit, Yref, Aref, crisp.Y_F32, "explicit, shape %d" % shape)
+        for rep in range(8):
+            at = rep * ((dact.numel() + 64) // 8 * 8)
+            moved = pool[at:at + dact.numel()]
+            moved.copy_(dact)
+            Y = torch.full((L.S, ld), float("nan"), dtype=torch.float32, device="cuda")
+            code = crisp.crisp_conv_spmm_forced(layer.desc, conv, layer.row_ptr, layer.col_idx, layer.vals, layer.idx_words,
+                                                moved, Y, ld, crisp.Y_F32, None, shape)
+            torch.cuda.synchronize()
+            fields = crisp.kernel_code_fields(code)
+            assert (fields["family"], fields["shape"], fields["conv_mode"]) == ("reg", split, 2)
+            got = Y.cpu().numpy().astype(np.float64)[:, :Ncol]
+            assert (got == explicit).all(), "shape %d, launch %d: %d outputs differ" % (shape, rep, int((got != explicit).sum()))
