@@ -405,7 +405,7 @@ template <> hipError_t launch_conv_lds_nm<8, 8>(const SpmmArgs&, const ConvLdsSc
 // Launch shape of the register-expansion kernels from the problem size (thresholds from sweeps
 // over the layer shapes of ResNet-50 at batch 256 and the small single-layer workloads):
 // wide strips once they give every SIMD work or the block-rows are long (the expansion of A is
-// shared by twice the columns); otherwise narrow strips; and when even those are few, 4 or 8
+// shared by twice the columns); otherwise narrow strips; and when even those are few, four
 // waves split each block-row's list so that enough loads are in flight to cover the latency.
 static int pick_shape(const Geometry& g, int64_t Ncol, int blocks_per_row, bool smf);
 
@@ -461,10 +461,12 @@ static int pick_shape(const Geometry& g, int64_t Ncol, int blocks_per_row, bool 
     if (blocks_per_row >= 8 && wide >= 512) return 0;
     if (narrow >= 3072 || blocks_per_row < 3) return 1;
     if (wide >= 512) return 0;
-    // the 8-way split keeps 8 partial tiles in LDS (128 KB for 64-row blocks: one workgroup per
-    // CU), so it only pays when all workgroups are resident at once
-    const int64_t resident8 = g.B == 64 ? 256 : 512;
-    if (blocks_per_row >= 8 && narrow <= resident8) return 3;
+    // few tiles: four waves split a tile's block list.  The split by eight (forced only) was chosen for rows of eight
+    // and more blocks while all its workgroups were resident; it is left alone since a build of it gave wrong products
+    // for a reason that was not found, and the split by four costs nothing for it: 3:4, 4:8 and 8:8, 9 to 144 blocks
+    // per row, 1 to 400 tiles, time over that of the split by eight 0.50-1.06 (512 x 2048 x 392 at half density, 64x64
+    // blocks: 7.6 against 9.9 us); convolutions with 32x32 blocks up to 1.07 (256 channels, 14x14, batch 1: 10.9
+    // against 10.2 us)
     return 2;
 }
 

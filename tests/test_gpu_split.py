@@ -46,3 +46,23 @@ def test_split_repeats_itself(n, m, B, geom):
             assert (fields["family"], fields["shape"], fields["conv_mode"]) == ("reg", split, 2)
             got = Y.cpu().numpy().astype(np.float64)[:, :Ncol]
             assert (got == explicit).all(), "shape %d, launch %d: %d outputs differ" % (shape, rep, int((got != explicit).sum()))
+
+
+@pytest.mark.parametrize("n,m", [(3, 4), (4, 4), (4, 8), (8, 8), (2, 4), (1, 8)])
+@pytest.mark.parametrize("B", [32, 64])
+def test_split_by_eight_is_never_the_librarys_choice(n, m, B):
+    """Few tiles and long block lists, where it used to be: plain X and a convolution."""
+    L = synth.LayerSpec("choice", 128, 1152, 196, n, m, B, 1.0, synth.SAL_MAG, 0.05)
+    rng = np.random.default_rng(n * 10 + m)
+    W = synth.draw_weight(rng, L)
+    layer, _ = run_select_pack(L, W, None)
+    X = torch.zeros((1152, 200), dtype=torch.int16, device="cuda")
+    Y = torch.empty((128, 200), dtype=torch.float32, device="cuda")
+    args = (layer.row_ptr, layer.col_idx, layer.vals, layer.idx_words, X)
+    plain = crisp.crisp_spmm_forced(layer.desc, *args, 196, 200, Y, 200, crisp.Y_F32, None, crisp.SHAPE_AUTO)
+    conv = crisp.crisp_conv_spmm_forced(layer.desc, crisp.ConvDesc(128, 14, 14, 1, 3, 3, 1, 1, crisp.ACT_CBHW, crisp.X_KN),
+                                        *args, Y, 200, crisp.Y_F32, None, crisp.SHAPE_AUTO)
+    torch.cuda.synchronize()
+    for code in (plain, conv):
+        fields = crisp.kernel_code_fields(code)
+        assert fields["family"] == "reg" and fields["shape"] == 2, fields
