@@ -28,6 +28,7 @@
 
 #include <hip/hip_ext.h>
 
+#include "conv_addr.h"
 #include "crisp_internal.h"
 
 namespace crisp {
@@ -87,9 +88,6 @@ struct XCtx {
     uint32_t sel_lo, sel_hi;
     uint32_t off2;   // conv mode 2: address part of the lane's second column
 };
-constexpr uint32_t SEL_LO = 0x05040100u;    // r0.lo | r1.lo << 16
-constexpr uint32_t SEL_HI = 0x07060302u;    // r0.hi | r1.hi << 16
-constexpr uint32_t SEL_ZERO = 0x0C0C0C0Cu;  // v_perm_b32: selector byte 0x0c yields 0x00
 
 // Output position (image, oh, ow) of a lane's first column in conv mode, fixed for the wave.
 struct ConvPos {
@@ -486,13 +484,8 @@ struct BlockBody {
     typedef typename XVec<XW>::type xvec_t;
     static constexpr int RT = F::RT, KS = F::KS, NACC = 2 * WD;
 
-    // Conv mode: context of block column bj.  All B K-rows of the block column belong to one
-    // filter tap (a, b) because C % B == 0.  The lane's two columns are output positions
-    // (oh, ow), (oh, ow+1) of one image; their sources are act[c][img][oh+a-pad][ow+b-pad (+1)].
-    // Both inside the image: one (possibly 2-byte-aligned) dword load.  Left border (only the
-    // second inside) or right border (only the first): the neighbouring in-row dword is loaded
-    // instead and the selectors pick the valid half and a zero.  Row outside: any valid address,
-    // selectors yield zeros.
+    // Conv mode: context of block column bj.  All B K-rows of the block column belong to one filter tap (a, b)
+    // because C % B == 0; conv_addr.h says where the lane's two columns of that tap lie and what is selected.
     __device__ static __forceinline__ XCtx conv_ctx(const SpmmArgs& p, const ConvPos& cp, int bj) {
         const int tap = (int)(((float)bj + 0.5f) * p.inv_cpb);
         const int a = (int)(((float)tap + 0.5f) * p.inv_kw);
@@ -517,50 +510,13 @@ struct BlockBody {
             return c;
         }
         if constexpr (CONV == 2) {
-            // each column on its own: source act[c][img][oh*stride + a - pad][ow*stride + b - pad]
-            // or, outside the image, any valid address and a selector that yields zeros
-            const int ih0 = cp.oh * p.stride + a - p.pad, iw0 = cp.ow * p.stride + b - p.pad;
-            const int ih1 = cp.oh1 * p.stride + a - p.pad, iw1 = cp.ow1 * p.stride + b - p.pad;
-            const bool v0 = (unsigned)ih0 < (unsigned)p.H && (unsigned)iw0 < (unsigned)p.W;
-            const bool v1 = (unsigned)ih1 < (unsigned)p.H && (unsigned)iw1 < (unsigned)p.W;
-            const int safe = (cp.img * p.H + cp.oh * p.stride) * p.W + cp.ow * p.stride;   // inside the image
-            const int s0 = v0 ? (cp.img * p.H + ih0) * p.W + iw0 : safe;
-            const int s1 = v1 ? (cp.img1 * p.H + ih1) * p.W + iw1 : safe;
-            XCtx c;
-            c.off = cp.half_off + (uint32_t)s0 * 2u;
-            c.off2 = cp.half_off + (uint32_t)s1 * 2u;
-            c.sel_lo = v0 ? SEL_LO : SEL_ZERO;
-            c.sel_hi = v1 ? SEL_LO : SEL_ZERO;
-            return c;
+            const PairSource s = pair_two_loads(p.H, p.W, p.pad, p.stride, (int)p.plane, OutPos{cp.img, cp.oh, cp.ow},
+                                                OutPos{cp.img1, cp.oh1, cp.ow1}, a, b);
+            return XCtx{cp.half_off + (uint32_t)s.off * 2u, s.sel_lo, s.sel_hi, cp.half_off + (uint32_t)s.off2 * 2u};
         }
-        // The lane's second column is the next output position, which may lie in the next output row or
-        // image (odd Wo).  The host picks this mode only where the two sources are then still neighbours in
-        // memory when both are inside the image: always inside one output row, and across rows and images
-        // when the padding is (k - 1) / 2 in both directions (then consecutive output positions read
-        // consecutive input elements for every tap).
-        const int ih = cp.oh + a - p.pad, iw = cp.ow + b - p.pad;
-        const int ih1 = cp.oh1 + a - p.pad, iw1 = cp.ow1 + b - p.pad;
-        const bool v0 = (unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W;
-        const bool v1 = (unsigned)ih1 < (unsigned)p.H && (unsigned)iw1 < (unsigned)p.W;
-        const int centre = (cp.img * p.H + cp.oh) * p.W + cp.ow;
-        const int src = (cp.img * p.H + ih) * p.W + iw;
-        const int src1 = (cp.img1 * p.H + ih1) * p.W + iw1;
-        XCtx c;
-        int off = centre;
-        c.sel_lo = SEL_ZERO;
-        c.sel_hi = SEL_ZERO;
-        if (v0 && v1) { off = src; c.sel_lo = SEL_LO; c.sel_hi = SEL_HI; }
-        else if (v1) {
-            // loaded (e0, e1) at the second column's source: column 1 <- e0; at the very end of a channel
-            // plane the dword one element earlier is loaded instead and column 1 <- e1
-            const bool last = (int64_t)src1 + 1 >= p.plane;
-            off = last ? src1 - 1 : src1;
-            c.sel_hi = last ? SEL_HI : SEL_LO;
-        }
-        else if (v0) { off = src - 1; c.sel_lo = SEL_HI; }   // loaded (e[src-1], e[src]): column 0 <- e[src]
-        c.off = cp.half_off + (uint32_t)off * 2u;
-        c.off2 = 0u;
-        return c;
+        const PairSource s = pair_one_load(p.H, p.W, p.pad, (int)p.plane, OutPos{cp.img, cp.oh, cp.ow},
+                                           OutPos{cp.img1, cp.oh1, cp.ow1}, a, b);
+        return XCtx{cp.half_off + (uint32_t)s.off * 2u, s.sel_lo, s.sel_hi, 0u};
     }
 
     // X rows of block column bj, MFMA step ks.  K is a multiple of 16 here, so a step lies either
