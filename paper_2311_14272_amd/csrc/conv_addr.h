@@ -31,7 +31,9 @@ __host__ __device__ __forceinline__ PairSource pair_one_load(int H, int W, int p
     const int ih1 = p1.oh + a - pad, iw1 = p1.ow + b - pad;
     const bool v0 = (unsigned)ih < (unsigned)H && (unsigned)iw < (unsigned)W;
     const bool v1 = (unsigned)ih1 < (unsigned)H && (unsigned)iw1 < (unsigned)W;
-    const int centre = (p0.img * H + p0.oh) * W + p0.ow;
+    // (the position itself as long as the padding is at most (k - 1) / 2; with more, output rows and columns go on past
+    // the image's and the last of them would lie past the plane)
+    const int centre = min((p0.img * H + p0.oh) * W + p0.ow, plane - 2);
     const int src = (p0.img * H + ih) * W + iw;
     const int src1 = (p1.img * H + ih1) * W + iw1;
     PairSource s = {centre, 0, SEL_ZERO, SEL_ZERO};
@@ -55,12 +57,11 @@ __host__ __device__ __forceinline__ PairSource pair_one_load(int H, int W, int p
 
 // Mode 2: each column on its own, one two-byte load each.
 __host__ __device__ __forceinline__ PairSource pair_two_loads(int H, int W, int pad, int stride, int plane, OutPos p0, OutPos p1, int a, int b) {
-    (void)plane;
     const int ih0 = p0.oh * stride + a - pad, iw0 = p0.ow * stride + b - pad;
     const int ih1 = p1.oh * stride + a - pad, iw1 = p1.ow * stride + b - pad;
     const bool v0 = (unsigned)ih0 < (unsigned)H && (unsigned)iw0 < (unsigned)W;
     const bool v1 = (unsigned)ih1 < (unsigned)H && (unsigned)iw1 < (unsigned)W;
-    const int safe = (p0.img * H + p0.oh * stride) * W + p0.ow * stride;
+    const int safe = min((p0.img * H + p0.oh * stride) * W + p0.ow * stride, plane - 1);
     return PairSource{v0 ? (p0.img * H + ih0) * W + iw0 : safe, v1 ? (p1.img * H + ih1) * W + iw1 : safe,
                       v0 ? SEL_LO : SEL_ZERO, v1 ? SEL_LO : SEL_ZERO};
 }

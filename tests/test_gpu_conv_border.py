@@ -12,7 +12,10 @@ from gpu_util import check_product, dev, run_select_pack
 pytestmark = pytest.mark.gpu
 
 # C, H, W, batch, kh, kw, stride, pad
-GEOMS = [(64, 4, 3, 2, 5, 5, 1, 2), (64, 3, 3, 4, 7, 7, 1, 3), (128, 2, 3, 2, 5, 5, 1, 2)]
+GEOMS = [(64, 4, 3, 2, 5, 5, 1, 2), (64, 3, 3, 4, 7, 7, 1, 3), (128, 2, 3, 2, 5, 5, 1, 2),
+         # padding of more than (k - 1) / 2: rows and columns of the output that see no input at all
+         (64, 6, 8, 2, 3, 3, 1, 2), (64, 5, 4, 2, 1, 1, 1, 2), (64, 6, 9, 2, 3, 1, 2, 3), (64, 7, 6, 2, 7, 1, 2, 3),
+         (128, 3, 6, 2, 1, 7, 1, 3)]
 
 
 @pytest.mark.parametrize("geom", GEOMS, ids=lambda g: "C%d_%dx%d_b%d_k%dx%d_s%d_p%d" % g)
