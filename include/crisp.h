@@ -355,6 +355,7 @@ CRISP_API crisp_status crisp_conv_spmm_ep(const crisp_layer_desc *desc, const cr
  * chosen by the caller, and a report of the kernel that ran.
  *   shape: CRISP_SHAPE_AUTO, or one of the shapes below; a shape that does not apply to the problem
  *          (pattern, block size, K or Ncol alignment, geometry) falls back to the automatic choice.
+ *          Plain X with K % 16 != 0 or Ncol % 4 != 0: shapes 1, 2, 4, 8 and 9 apply.
  *   kernel_code (optional, host): receives family | shape << 8 | conv_mode << 16 | sparse << 24 of
  *          the kernel that was launched (family: CRISP_KERNEL_*; shape: the register kernels' launch
  *          shape 0..3; for the LDS-resident family bit 0 = wide strips, bit 1 = the instantiation with

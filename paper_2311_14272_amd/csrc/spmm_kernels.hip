@@ -757,12 +757,17 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
     // row under at most 16 block-rows and many tiles (512 x 2305 x 50003 1:8 at 0.7: 364 against 419 us), where the
     // generic kernel's wide strips fetch a block's slices once for 512 columns; there it stays.
     const bool long_b32 = g.B == 32 && g.n <= 2 && bpr >= 10 && g.Sb <= 16 && (int64_t)g.Sb * ((Ncol + 63) / 64) >= 1024;
-    if (!conv && force_shape < 0 && !long_b32 && ld_wide <= ((int64_t)1 << 23) && ldx <= ((int64_t)1 << 23)) {
+    // Forced narrow strips and the split by four exist here too (1, 2 and 8, 9); any other forced shape but the
+    // generic one does not apply and leaves the choice to the rule.
+    const bool forced_r = force_shape == CRISP_SHAPE_REG_NARROW || force_shape == CRISP_SHAPE_REG_SPLIT4 ||
+                          force_shape == CRISP_SHAPE_SMF_NARROW || force_shape == CRISP_SHAPE_SMF_SPLIT4;
+    if (!conv && force_shape != CRISP_SHAPE_GENERIC && (forced_r || !long_b32) && ld_wide <= ((int64_t)1 << 23) &&
+        ldx <= ((int64_t)1 << 23)) {
         a.ragged = 1;
-        a.use_smf = 1;
-        const int shape_r = shape <= 1 ? 1 : 2;
+        a.use_smf = !(forced_r && force_shape <= CRISP_SHAPE_REG_SPLIT4);
+        const int shape_r = forced_r ? shape : pick_shape(g, Ncol, bpr, smf_ok) <= 1 ? 1 : 2;
         auto run = [&](auto launch) {
-            report(CRISP_KERNEL_REG, shape_r, 0, smf_ok);
+            report(CRISP_KERNEL_REG, shape_r, 0, a.use_smf && smf_ok);
             return launch();
         };
         switch (g.n * 16 + g.m) {

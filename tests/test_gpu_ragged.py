@@ -49,3 +49,39 @@ def test_ragged_product(n, m, B, S, K, N, ep, topk):
     assert float((y - ref).abs().max()) <= 2.0 ** -24 * (K * 0.1 * K * 0.6 + 64)
     yb, _ = product(torch.bfloat16, crisp.SHAPE_AUTO)
     assert torch.equal(y.to(torch.bfloat16), yb)
+
+
+@pytest.mark.parametrize("n,m", [(1, 4), (2, 4), (3, 4), (2, 8), (4, 8)])
+@pytest.mark.parametrize("B", [32, 64])
+@pytest.mark.parametrize("S,K,N", [(70, 147, 131), (130, 1000, 257), (96, 640, 66)])
+def test_forced_shapes(n, m, B, S, K, N):
+    """Narrow strips and the split by four can be forced on ragged problems, with and without the sparse instruction;
+    a shape that does not apply leaves the choice to the library, whose kernel and bits it then has."""
+    g = torch.Generator(device="cuda").manual_seed(S + K + N)
+    layer = crisp.alloc_layer(crisp.layer_desc(S, K, n, m, B, 0.6, crisp.SAL_MAG))
+    W = (torch.randn((S, K), generator=g, device="cuda") * 0.1).to(torch.bfloat16).view(torch.int16)
+    crisp.prune_and_pack(layer, W, None)
+    ld = (N + 7) // 8 * 8
+    X = torch.randn((K, ld), generator=g, device="cuda").to(torch.bfloat16).view(torch.int16)
+
+    def product(shape):
+        Y = torch.full((S, ld), float("nan"), dtype=torch.float32, device="cuda")
+        code = crisp.crisp_spmm_forced(layer.desc, layer.row_ptr, layer.col_idx, layer.vals, layer.idx_words, X, N, ld, Y, ld,
+                                       crisp.Y_F32, None, shape)
+        torch.cuda.synchronize()
+        f = crisp.kernel_code_fields(code)
+        return Y[:, :N], (f["family"], f["shape"], f["sparse_mfma"])
+
+    ref, kernel = product(4)
+    assert kernel[0] == "generic"
+    auto, chosen = product(crisp.SHAPE_AUTO)
+    sparse = int(n <= 2)
+    for shape, want in ((1, ("reg", 1, 0)), (2, ("reg", 2, 0)), (8, ("reg", 1, sparse)), (9, ("reg", 2, sparse))):
+        y, kernel = product(shape)
+        assert kernel == want, shape
+        # (the bound of test_ragged_product)
+        assert float((y - ref).abs().max()) <= 2.0 ** -24 * (K * 0.1 * K * 0.6 + 64), shape
+    for shape in (0, 3, 5, 6, 7, 10, 13, 15, 16, 17, 18):
+        y, kernel = product(shape)
+        assert kernel == chosen, shape
+        assert torch.equal(y, auto), shape
