@@ -288,6 +288,11 @@ CRISP_API crisp_status crisp_im2col(const crisp_conv_desc *conv, const uint16_t 
  *   correctness.
  *   ws, ws_bytes: reserved (spmm_ws_bytes is 0); both are ignored.  Results of the launch
  *   shapes the library may choose agree within the summation-order tolerance.
+ *   Infinite or NaN elements of X: kernels may multiply them by the zeros that stand for dropped
+ *   positions of a kept block (NaN) or leave them out, and with the sparse matrix-core instruction
+ *   an infinity at a kept position of a 1:m or 2:8 layer may become NaN when K % 16 == 0 and
+ *   Ncol % 4 == 0.  With other K or Ncol an output that dense multiplication of the kept blocks
+ *   leaves finite or infinite is exactly that.
  * Errors: EINVAL, ESHAPE, EALIGN, EUNSUPPORTED (x_layout and what it covers), EDEVICE.
  */
 CRISP_API crisp_status crisp_spmm(const crisp_layer_desc *desc, const int32_t *row_ptr, const int32_t *col_idx,

@@ -452,6 +452,20 @@ __device__ __forceinline__ void smf_operand(const uint32_t (&av)[Fmt<N, M, B>::K
     }
 }
 
+// The index register with no zero partner left at the position of a stored value: of two equal positions in a four the
+// one that belongs to the zero moves to a neighbouring column (a zero of the upper four of a 2:8 group stands first, every
+// other one second).  An infinite element of X at a kept column is then multiplied by its weight alone and not also by
+// zero; at a dropped column of a kept block the product is NaN or left out, as a dense expansion would have it NaN.
+// Six integer operations per operand at most; the ragged kernels alone do this, which took over from the generic one.
+template <int N, int M>
+__device__ __forceinline__ uint32_t smf_apart(uint32_t idx) {
+    if constexpr (N == 1) return idx ^ 0x4444u;
+    const uint32_t x = idx ^ (idx >> 2);
+    const uint32_t equal = ~(x | (x >> 1));            // bit 4i: both positions of four i are the same
+    if constexpr (N == 2 && M == 8) return idx ^ ((equal & 0x0101u) << 2) ^ (equal & 0x1010u);
+    return idx ^ ((equal & 0x1111u) << 2);
+}
+
 // One kept block: multiply the block held in ring slot (xr, av, aw) into acc.  With PREFETCH the
 // X rows of block column bj_next are requested into the same registers as soon as their
 // current contents have been turned into MFMA operands, and block t_next's compressed slice
@@ -716,6 +730,7 @@ struct BlockBody {
             u32x4 a4;
             uint32_t idx;
             smf_operand<N, M, B, s2>(av[rt], ws[rt], a4, idx);
+            if constexpr (CONV == 6) idx = smf_apart<N, M>(idx);
             const bf16x8 afrag = __builtin_bit_cast(bf16x8, a4);
 #pragma unroll
             for (int c = 0; c < NACC; ++c) {

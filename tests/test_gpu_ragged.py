@@ -85,3 +85,40 @@ def test_forced_shapes(n, m, B, S, K, N):
         y, kernel = product(shape)
         assert kernel == chosen, shape
         assert torch.equal(y, auto), shape
+
+
+@pytest.mark.parametrize("n,m", [(1, 4), (2, 4), (3, 4), (4, 4), (1, 8), (2, 8), (4, 8), (8, 8)])
+@pytest.mark.parametrize("B", [32, 64])
+@pytest.mark.parametrize("K,N", [(129, 66), (163, 7), (1000, 130)])
+def test_infinite_activations(n, m, B, K, N):
+    """An infinite element of X: wherever the generic kernel's result is a number or an infinity, the ragged register
+    kernels have the same infinity or a number within the bound of test_ragged_product.  The last row of X, which lies
+    in a short group for two of the sizes, is among the infinite ones."""
+    S = 96
+    g = torch.Generator(device="cuda").manual_seed(K + N)
+    layer = crisp.alloc_layer(crisp.layer_desc(S, K, n, m, B, 1.0, crisp.SAL_MAG))
+    W = (torch.randn((S, K), generator=g, device="cuda") * 0.1).to(torch.bfloat16).view(torch.int16)
+    crisp.prune_and_pack(layer, W, None)
+    ld = (N + 7) // 8 * 8
+    Xf = torch.randn((K, ld), generator=g, device="cuda")
+    for i, k in enumerate(list(range(0, K, 17)) + [K - 1]):
+        Xf[k, i % N] = float("inf") if i % 2 else float("-inf")       # few rows per column: most have one at most
+    X = Xf.to(torch.bfloat16).view(torch.int16)
+
+    def product(shape):
+        Y = torch.zeros((S, ld), dtype=torch.float32, device="cuda")
+        code = crisp.crisp_spmm_forced(layer.desc, layer.row_ptr, layer.col_idx, layer.vals, layer.idx_words, X, N, ld, Y, ld,
+                                       crisp.Y_F32, None, shape)
+        torch.cuda.synchronize()
+        return Y[:, :N], crisp.kernel_code_fields(code)["family"]
+
+    ref, family = product(4)
+    assert family == "generic"
+    assert bool(torch.isinf(ref).any())
+    inf, fin = torch.isinf(ref), torch.isfinite(ref)
+    for shape in (crisp.SHAPE_AUTO, 1, 2, 8, 9):
+        y, family = product(shape)
+        assert family == "reg"
+        assert torch.equal(y[inf], ref[inf]), "shape %d: %d of %d infinities lost" % (shape, int((y[inf] != ref[inf]).sum()), int(inf.sum()))
+        if bool(fin.any()):
+            assert float((y[fin] - ref[fin]).abs().max()) <= 2.0 ** -24 * (K * 0.1 * K * 0.6 + 64), shape
