@@ -347,8 +347,10 @@ __device__ __forceinline__ u32x4 expand_frag(const uint32_t (&v)[Fmt<N, M, B>::V
 // group's 8-bit occupancy mask names the layout, and the j-th stored value belongs to the j-th set bit.  The
 // table (256 entries of four v_perm_b32 selectors, 4 KB of LDS, built once per workgroup) turns the two stored
 // dwords straight into the four operand dwords: 4 bit-field extracts, 4 shift-ors, one 16-byte LDS read and 4
-// permutes instead of about 76 vector instructions.  Needs whole groups (K a multiple of 8: the specialised
-// kernels require 16); groups wholly past K or S hold zeros at positions 0..3, which the same rule covers.
+// permutes instead of about 76 vector instructions.  Groups wholly past K or S hold zeros at positions 0..3,
+// which the same rule covers.  A short last group (K no multiple of 8, the ragged kernels) keeps its columns
+// 0..r-1 when it has r <= 4 of them and four of them otherwise, as a full one does; the unused slots of the former hold
+// zero at position 0, which adds nothing to the mask, so the j-th stored value still belongs to the j-th set bit.
 // Entry of mask m, operand dword x: low half from position 2x, high half from 2x + 1; a position that is the
 // r-th set bit of m takes bytes 2r, 2r + 1 of the stored pair (v_perm_b32 numbers the second source's bytes
 // 0..3 and the first's 4..7), an empty position the selector 0x0c (zero).
@@ -402,7 +404,9 @@ __device__ __forceinline__ void smf_operand(const uint32_t (&av)[Fmt<N, M, B>::K
             // full group of eight holds exactly two in its lower and two in its upper four, stored in ascending
             // column order, so the stored values are the operand as they are (like 2:4) and a value's position
             // inside its four is the low two bits of its 3-bit position.  (Groups past K or S hold zeros at
-            // positions 0..3: two "values" per four as well.)
+            // positions 0..3: two "values" per four as well.  A short last group can only pass the flag with one or
+            // two columns -- one or two values at positions 0, 1, then zeros at position 0, whose products are
+            // zero -- or with six or seven, of which it keeps two per four like a full one.)
             a4 = u32x4{av[2 * s2][0], av[2 * s2][1], av[2 * s2 + 1][0], av[2 * s2 + 1][1]};
             idx = 0;
 #pragma unroll
@@ -533,9 +537,10 @@ struct BlockBody {
         return XCtx{cp.half_off + (uint32_t)s.off * 2u, s.sel_lo, s.sel_hi, 0u};
     }
 
-    // X rows of block column bj, MFMA step ks.  K is a multiple of 16 here, so a step lies either
-    // wholly inside the matrix or wholly past its end; a step past the end re-reads the last 16
-    // rows instead (finite values times the zero padding of the packed block).
+    // X rows of block column bj, MFMA step ks.  K is a multiple of 16 except with CONV 3 and 6, so a step lies
+    // either wholly inside the matrix or wholly past its end; a step past the end re-reads the last 16
+    // rows instead (finite values times the zero padding of the packed block).  CONV 3 and 6 let the range of
+    // the buffer resource turn rows past K into zeros.
     __device__ static __forceinline__ void load_x(xvec_t (&dst)[8], const SpmmArgs& p, const ConvPos& cp,
                                                    uint32_t lane_off, uint32_t lane_off2, int bj, int ks) {
         if constexpr (CONV == 5) {
@@ -788,7 +793,8 @@ struct BlockBody {
 // columns).  row_source(pr, v) fills v with the lane's NACC values of that row.  Y is written
 // through a buffer resource that spans the block-row's existing rows: rows past S and lanes past
 // the last column fall outside its range and the hardware drops them, so the stores need no
-// branches.  (Ncol is a multiple of 4 here, so a lane's columns are all inside or all outside.)
+// branches.  (Ncol is a multiple of 4 there -- of 2 with two columns per lane -- so that a lane's columns are all
+// inside or all outside, except with RAGGED.)
 // The four (epilogue yes/no) x (bf16/fp32 output) variants of the store loop are separate copies
 // chosen once per wave, so the loop itself holds no branches; with an epilogue its operands are
 // requested for a batch of rows before the first of them is used.

@@ -62,6 +62,38 @@ def test_hint_sends_4_of_8_to_the_sparse_instruction(case):
     layer.desc = plain
 
 
+@pytest.mark.parametrize("K", [129, 130, 134, 135, 168, 641, 646])
+@pytest.mark.parametrize("B,Ncol", [(32, 131), (64, 131), (64, 66)])
+def test_hint_on_ragged_products(K, B, Ncol):
+    """K that ends inside a group of eight (one, two, six or seven columns: the lengths at which the kept columns can
+    still fall two per aligned four) or inside a 16-row step, and column counts that are no multiple of four: the
+    sparse instruction of the ragged register kernels against the oracle."""
+    S = 100
+    L = synth.LayerSpec("two_of_four_ragged", S, K, Ncol, 4, 8, B, 0.75, synth.SAL_MAG, 1.0)
+    rng = np.random.default_rng(K + B)
+    W = np.ascontiguousarray(synth.draw_two_per_quad_weight(rng, S, (K + 3) // 4 * 4)[:, :K])
+    tail = K % 4                       # the cut four: its first two columns are the ones kept
+    if tail:
+        W[:, K - tail:] = synth.f32_to_bf16_bits(np.array([2.5, -2.75, 0.25], dtype=np.float32)[:tail])
+    X = synth.draw_relu_normal(rng, (K, Ncol))
+    sel = oracle.select(W, None, 4, 8, B, 0.75, synth.SAL_MAG, synth.ROW_UNIFORM)
+    layer, out = run_select_pack(L, W, None)
+    assert int(out["flags"][0]) == 1
+    Yref, Aref = oracle.gemm_masked(W, sel.mask, X)
+    ldx = (Ncol + 7) // 8 * 8
+    Xp = np.full((K, ldx), 0x7FC0, dtype=np.uint16)      # NaN past the last column: must not leak
+    Xp[:, :Ncol] = X
+    dX = dev(Xp)
+    layer.desc = crisp.layer_desc(S, K, 4, 8, B, 0.75, synth.SAL_MAG, synth.ROW_UNIFORM, hints=crisp.HINT_TWO_OF_FOUR)
+    for shape, sparse in ((crisp.SHAPE_AUTO, 1), (8, 1), (9, 1), (1, 0), (2, 0)):
+        Y32, code = run_spmm(layer, dX, Ncol, ldx, crisp.Y_F32, S, shape=shape, with_code=True)
+        fields = crisp.kernel_code_fields(code)
+        assert (fields["family"], fields["sparse_mfma"]) == ("reg", sparse), (shape, fields)
+        check_product(Y32, Yref, Aref, crisp.Y_F32, "shape %s" % shape)
+        Y16 = run_spmm(layer, dX, Ncol, ldx, crisp.Y_BF16, S, shape=shape)
+        check_bf16_is_rounded_f32(Y16, Y32, "shape %s" % shape)
+
+
 def test_hint_is_ignored_for_other_patterns():
     """The hint on a 2:4 layer (always eligible) and on a 3:4 layer (never): same kernels, same bits as without."""
     for (n, m) in ((2, 4), (3, 4)):
