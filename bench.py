@@ -14,10 +14,12 @@ configuration; one layer's inputs and outputs alone exceed the last-level cache,
                         launch / its average launch duration from HIP event pairs recorded around
                         its launches inside the timed steps;
   cpu_baseline          the CPU oracle timed on the host cores on a bounded sample of the workload;
-  layers                per-layer time, useful TFLOP/s, fraction of the HBM / MFMA bound;
   configs               one row per benchmark configuration 1..5 (1..4 measured after the timed
                         region by short runs of their own; --no-config-table skips them).
-`--config 1..4` makes one of the small configurations the workload of the line instead.
+`--config 1..4` makes one of the small configurations the workload of the line instead.  `--details FILE`
+writes the whole record, with per-layer time, useful TFLOP/s and fraction of the HBM / MFMA bound, the
+configurations' layers and the input digests: with them the line would be over 20 KB, more than a reader that
+keeps the end of the output gets to see whole.
 """
 from __future__ import annotations
 
@@ -47,6 +49,7 @@ def parse():
                     help="workload 1..5 (default 5: all 53 ResNet-50 convs at batch 256, the largest configuration)")
     ap.add_argument("--sets", type=int, default=0, help="configs 1..4: independent input sets to rotate through (0 = enough for 600 MB)")
     ap.add_argument("--y-dtype", choices=["bf16", "f32"], default="bf16")
+    ap.add_argument("--details", default=None, metavar="FILE", help="write the whole record (per-layer rows, input digests) to FILE")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-config-table", action="store_true", help="skip the short runs of the other configurations")
     ap.add_argument("--spmm-only", action="store_true", help="configs 1..4: time only the products (selection and packing done once)")
@@ -873,6 +876,17 @@ def block_sweep(args):
                                "rotating input sets)", "workload": wl.name, "y_dtype": args.y_dtype, "rows": rows}))
 
 
+def emit(out, args):
+    """The line, without what only --details holds."""
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(out, f, indent=1)
+    line = {k: v for k, v in out.items() if k not in ("layers", "inputs", "configs")}
+    if "configs" in out:
+        line["configs"] = [{k: v for k, v in row.items() if k != "layers"} for row in out["configs"]]
+    print(json.dumps(line))
+
+
 def main():
     args = parse()
     if args.gpus != 1:
@@ -893,8 +907,7 @@ def main():
         return
     want_cpu = not args.no_cpu_baseline
     if args.config != 5:
-        out = run_small(args.config, args, args.steps or 200, args.warmup or 20, "full" if want_cpu else None)
-        print(json.dumps(out))
+        emit(run_small(args.config, args, args.steps or 200, args.warmup or 20, "full" if want_cpu else None), args)
         return
     out, useful = run_resnet50(args)
     if want_cpu and not args.chained:
@@ -906,7 +919,7 @@ def main():
             table.append(config_row(cid, run_small(cid, args, 100, 10, "short" if want_cpu else None)))
         table.append(config_row(5, out))
         out["configs"] = table
-    print(json.dumps(out))
+    emit(out, args)
 
 
 if __name__ == "__main__":
