@@ -424,17 +424,29 @@ static bool conv_lds_reuses(const ConvLdsSched& s, int Sb, double density, int b
     return blocks_per_patch >= 6.0 && Sb <= 4 && Wo <= 28 && wgs >= 256;
 }
 
-// And whether it is launched: its waves keep one tile for all kept blocks, so few workgroups leave compute units
-// idle for that long, while the register kernels can split a tile's block list over four waves.  Measured on 3x3
-// layers of 128 to 512 channels at 14x14 ... 56x56, batch 1 to 256, 1:8, 2:4, 4:8 and 3:4, time over that of the
-// best register shape.  Stride 1: density 0.6, up to 64 workgroups 2.2-3.6 (256 channels, 14x14, batch 8: 24.4
-// against 9.8 us), 112-128 1.5-2.2, 224-256 0.95-1.4, 448-512 0.64-1.05; density 0.3, 256 1.2-1.6, 448 1.0-1.3,
-// 896 0.86-1.1.  Stride 2, where the register kernels fetch every element by itself: density 0.6, 32 workgroups
-// 1.9-2.4, 128 1.0-1.4, 512 0.41-0.59; density 0.3, 128 1.6-2.2, 512 0.68-0.88.
-static bool conv_lds_pays(const ConvLdsSched& s, int Sb, double density, int batch, int Wo, int stride) {
-    const int64_t wgs = (int64_t)batch * s.tiles_per_img * s.row_groups;
-    const int64_t least = stride == 1 ? (density >= 0.5 ? 384 : 640) : (density >= 0.5 ? 192 : 256);
-    return conv_lds_reuses(s, Sb, density, batch, Wo) && wgs >= least;
+// Whether the register kernels run such a convolution all the same: the staged kernel's waves keep one tile for all
+// kept blocks, so few workgroups leave compute units idle for that long, while the register kernels split a tile's
+// block list over four waves.  Measured on 3000 random geometries with fewer than 700 workgroups (3x3, 5x5 and 7x7
+// filters, stride 1 to 4, 64 to 512 channels, images of 4x4 to 64x64, batch 1 to 64, all patterns, densities from 0.2):
+//   stride 1, below 192 workgroups (7x7: 128): register over staged 0.23-1.00 of the time, 0.5 in the middle; from 192 to
+//     383 it is 0.53-1.86 and the staged kernel stays, except below half density (0.55-0.93); beyond, 0.69-2.99;
+//   with a stride the register kernels fetch every element by itself: 0.29-1.0 for 3x3 filters, output rows of six and
+//     more, below 128 workgroups and 256 tiles; up to 2.6 for larger filters, more tiles or shorter rows (256 channels,
+//     8x8, stride 2, batch 16, 1:8: 38 against 28 us), where the staged kernel stays.  Patterns of the sparse
+//     instruction leave out planes of 2^k elements or a small odd multiple of a large one (up to 1.59: 384 channels,
+//     16x16, batch 64: 57 against 43 us); planes of 25, 49 ... times a power of two, as networks have them, are well.
+static bool conv_regs_split(const ConvLdsSched& s, const SpmmArgs& a, double density, int64_t wgs, bool sparse) {
+    if (a.stride == 1) return wgs < (density < 0.5 ? 384 : s.taps <= 25 ? 192 : 128);
+    const int64_t tiles = (int64_t)a.Sb * ((a.Ncol + 63) / 64);
+    const int64_t low_bit = a.plane & -a.plane;
+    const bool spread = low_bit < 256 || a.plane / low_bit >= 25;
+    return density >= 0.5 && s.taps <= 9 && a.Wo >= 6 && wgs < 128 && tiles < 256 && (!sparse || spread);
+}
+
+// And whether it is launched.
+static bool conv_lds_pays(const ConvLdsSched& s, const SpmmArgs& a, double density, int batch, bool sparse) {
+    return conv_lds_reuses(s, a.Sb, density, batch, a.Wo) &&
+           !conv_regs_split(s, a, density, (int64_t)batch * s.tiles_per_img * s.row_groups, sparse);
 }
 
 static int pick_shape(const Geometry& g, int64_t Ncol, int blocks_per_row, bool smf) {
@@ -607,7 +619,7 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
     ConvLdsSched cs;
     const bool conv_lds_wanted = force_shape == 12 || force_shape < 0;
     if (conv && conv_lds_wanted && (Ncol % 4) == 0 && ld_wide <= ((int64_t)1 << 23) && conv_lds_plan(a, g.B, conv->kh, &cs) &&
-        (force_shape == 12 || conv_lds_pays(cs, g.Sb, density_hint, conv->batch, a.Wo, a.stride))) {
+        (force_shape == 12 || conv_lds_pays(cs, a, density_hint, conv->batch, g.n <= 2))) {
         a.use_smf = 1;
         report(CRISP_KERNEL_CONV_LDS, 0, a.conv_mode, g.n <= 2);
         switch (g.n * 16 + g.m) {

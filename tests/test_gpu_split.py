@@ -66,3 +66,37 @@ def test_split_by_eight_is_never_the_librarys_choice(n, m, B):
     for code in (plain, conv):
         fields = crisp.kernel_code_fields(code)
         assert fields["family"] == "reg" and fields["shape"] == 2, fields
+
+
+# C, S, H, batch, k, stride, density, n, m: the kernel that stages the input where it is the faster one (after #, us of
+# the register kernels / staged), the register kernels' split by four where few workgroups would leave it idle
+@pytest.mark.parametrize("case,family", [
+    ((128, 768, 28, 8, 5, 1, 1.0, 2, 4), "conv_lds"),       # 102 / 43
+    ((128, 256, 8, 16, 7, 2, 0.8, 2, 4), "conv_lds"),       # 76 / 46
+    ((64, 256, 8, 8, 5, 2, 1.0, 2, 4), "conv_lds"),         # 27 / 18
+    ((256, 192, 8, 32, 5, 4, 1.0, 8, 8), "conv_lds"),       # 195 / 75
+    ((384, 256, 16, 64, 3, 2, 1.0, 1, 4), "conv_lds"),      # 57 / 43: planes of 2^14 elements
+    ((256, 256, 14, 8, 3, 1, 0.6, 2, 4), "reg"),            # 10 / 24
+    ((128, 128, 56, 8, 3, 2, 0.6, 2, 4), "reg"),            # 12 / 20
+    ((512, 512, 8, 8, 3, 1, 0.6, 3, 4), "reg"),             # 17 / 66
+], ids=str)
+def test_choice_for_few_workgroups(case, family):
+    C_, S, H, b, k, stride, dens, n, m = case
+    cv = synth.ConvShape(C_, H, H, b, k, k, stride, k // 2)
+    layer = crisp.alloc_layer(crisp.layer_desc(S, cv.K, n, m, 64, dens, crisp.SAL_MAG))
+    g = torch.Generator(device="cuda").manual_seed(C_)
+    W = (torch.randn((S, cv.K), generator=g, device="cuda") * 0.05).to(torch.bfloat16).view(torch.int16)
+    crisp.prune_and_pack(layer, W, None)
+    act = torch.randn((C_, b, H, H), generator=g, device="cuda").to(torch.bfloat16).view(torch.int16)
+    ld = (cv.Ncol + 7) // 8 * 8
+    out = []
+    for shape in (crisp.SHAPE_AUTO, 12, 2):
+        Y = torch.full((S, ld), float("nan"), dtype=torch.float32, device="cuda")
+        code = crisp.crisp_conv_spmm_forced(layer.desc, crisp.conv_desc_of(cv), layer.row_ptr, layer.col_idx, layer.vals,
+                                            layer.idx_words, act, Y, ld, crisp.Y_F32, None, shape)
+        torch.cuda.synchronize()
+        out.append((crisp.kernel_code_fields(code)["family"], Y[:, :cv.Ncol]))
+    assert out[0][0] == family
+    for _, y in out[1:]:
+        # the same products in another order: relative 2-norm as of the fp32 tripwire of the parity tests
+        assert float((y - out[0][1]).norm() / y.norm()) <= 1e-5
