@@ -763,12 +763,17 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
         if (conv) return hipErrorInvalidValue;  // callers check the pattern first
     }
     // Plain X whose K is no multiple of 16 or whose Ncol is none of 4: the register kernels with ranged resources
-    // (narrow strips, or the split by four).  Against the generic kernel, bf16 output, densities 0.3 and 0.7, 1:8, 2:4,
-    // 4:8 and 3:4: 64x64 blocks 1.24-5.0x (512 x 2305 x 50003 2:4 276 -> 130 us at 0.3; 256 x 1153 x 197 59 -> 12 us at
-    // 0.7), 32x32 blocks 1.02-4.0x -- but 0.87-0.98x for patterns of the sparse instruction with ten or more blocks per
-    // row under at most 16 block-rows and many tiles (512 x 2305 x 50003 1:8 at 0.7: 364 against 419 us), where the
-    // generic kernel's wide strips fetch a block's slices once for 512 columns; there it stays.
-    const bool long_b32 = g.B == 32 && g.n <= 2 && bpr >= 10 && g.Sb <= 16 && (int64_t)g.Sb * ((Ncol + 63) / 64) >= 1024;
+    // (narrow strips, or the split by four).  Time over that of the generic kernel on 1267 random products (S 4 to 2300,
+    // K 16 to 4700, up to 130 thousand columns, all patterns and densities, bf16 and fp32 output): 0.14-1.00 with 64x64
+    // blocks or patterns of dense expansion, 0.4 in the middle (512 x 2305 x 50003 2:4, 64x64 blocks: 130 against 276
+    // us); with 32x32 blocks and the sparse instruction 0.21-0.87 below 512 tiles, but up to 1.52 on many tiles (699 x 4401 x
+    // 5100 1:8: 72 against 47 us), where the generic kernel's wide strips fetch a block's slices and its lines of X once
+    // for up to 512 columns.  There rows of up to four blocks run here (0.49-1.05), and rows of up to nine for bf16 output,
+    // an X that the last-level cache holds several times over and patterns other than 1:8 (0.56-1.03); the rest stays.
+    const int64_t tiles_r = (int64_t)g.Sb * ((Ncol + 63) / 64);
+    const bool many = tiles_r >= 1024 && bpr > 4 &&
+                      !(a.y_bf16 && (int64_t)g.K * ldx * 2 < ((int64_t)48 << 20) && 8 * g.n / g.m > 1 && bpr < 10);
+    const bool long_b32 = g.B == 32 && g.n <= 2 && (many || (tiles_r >= 512 && bpr >= 14));
     // Forced narrow strips and the split by four exist here too (1, 2 and 8, 9); any other forced shape but the
     // generic one does not apply and leaves the choice to the rule.
     const bool forced_r = force_shape == CRISP_SHAPE_REG_NARROW || force_shape == CRISP_SHAPE_REG_SPLIT4 ||

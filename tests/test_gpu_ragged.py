@@ -122,3 +122,28 @@ def test_infinite_activations(n, m, B, K, N):
         assert torch.equal(y[inf], ref[inf]), "shape %d: %d of %d infinities lost" % (shape, int((y[inf] != ref[inf]).sum()), int(inf.sum()))
         if bool(fin.any()):
             assert float((y[fin] - ref[fin]).abs().max()) <= 2.0 ** -24 * (K * 0.1 * K * 0.6 + 64), shape
+
+
+# S, K, N, n, m, density, bf16: on many tiles with 32x32 blocks and the sparse instruction the generic kernel stays for long
+# rows, fp32 output and 1:8 (us of the register kernels / generic: 72 / 47, 205 / 139, 221 / 185), else it does not
+@pytest.mark.parametrize("case,family", [((699, 4401, 5100, 1, 8, 0.2, 1), "generic"), ((1112, 2616, 3553, 2, 4, 1.0, 0), "generic"),
+                                         ((1102, 541, 20837, 1, 8, 0.3, 0), "generic"), ((203, 459, 25003, 2, 4, 0.5, 1), "reg"),
+                                         ((64, 147, 70001, 1, 8, 0.5, 0), "reg")], ids=str)
+def test_choice_with_32_row_blocks(case, family):
+    S, K, N, n, m, dens, bf16 = case
+    g = torch.Generator(device="cuda").manual_seed(S)
+    layer = crisp.alloc_layer(crisp.layer_desc(S, K, n, m, 32, dens, crisp.SAL_MAG))
+    W = (torch.randn((S, K), generator=g, device="cuda") * 0.05).to(torch.bfloat16).view(torch.int16)
+    crisp.prune_and_pack(layer, W, None)
+    ld = (N + 7) // 8 * 8
+    X = torch.randn((K, ld), generator=g, device="cuda").to(torch.bfloat16).view(torch.int16)
+    out = []
+    for shape in (crisp.SHAPE_AUTO, 4):
+        Y = torch.full((S, ld), float("nan"), dtype=torch.bfloat16 if bf16 else torch.float32, device="cuda")
+        code = crisp.crisp_spmm_forced(layer.desc, layer.row_ptr, layer.col_idx, layer.vals, layer.idx_words, X, N, ld, Y, ld,
+                                       crisp.Y_BF16 if bf16 else crisp.Y_F32, None, shape)
+        torch.cuda.synchronize()
+        out.append((crisp.kernel_code_fields(code)["family"], Y[:, :N].float()))
+    assert out[0][0] == family and out[1][0] == "generic"
+    # the same products in another order, and for bf16 the roundings of either (1.66e-3 each of a result)
+    assert float((out[0][1] - out[1][1]).norm() / out[1][1].norm()) <= (2 * 1.66e-3 if bf16 else 1e-5)
