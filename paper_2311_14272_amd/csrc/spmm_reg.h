@@ -808,10 +808,9 @@ __device__ __forceinline__ void store_rows(const SpmmArgs& p, int bi, int hh, in
     const int rows_here = min(B, p.S - bi * B);
     const rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(
         reinterpret_cast<char*>(p.Y) + (int64_t)bi * B * p.ldy * esz, 0, (uint32_t)rows_here * row_bytes, 0x00020000);
-    const uint32_t y_lane = (uint32_t)(4 * hh) * row_bytes + (uint32_t)col0 * esz;
     const bool straddles = RAGGED && col_ok && col0 + NACC > p.Ncol;
     const bool any_straddles = RAGGED && __any(straddles);
-    const uint32_t y_off = (col_ok && !straddles) ? y_lane : 0x80000000u;
+    const uint32_t y_off = (col_ok && !straddles) ? (uint32_t)(4 * hh) * row_bytes + (uint32_t)col0 * esz : 0x80000000u;
     auto tile_row_of = [&](int q) __attribute__((always_inline)) {
         const int pr = row_first + q * ROW_STEP;
         return (pr >> 4) * 32 + 8 * ((pr & 15) >> 2) + (pr & 3);
@@ -822,6 +821,7 @@ __device__ __forceinline__ void store_rows(const SpmmArgs& p, int bi, int hh, in
             const uint32_t off = y_off + (uint32_t)tile_row * row_bytes;
             if constexpr (RAGGED) {
                 if (any_straddles) {
+                    const uint32_t y_lane = (uint32_t)(4 * hh) * row_bytes + (uint32_t)col0 * esz;
 #pragma unroll
                     for (int c = 0; c + 1 < NACC; ++c) {
                         const uint32_t one = (straddles && col0 + c < p.Ncol) ? y_lane + (uint32_t)c * esz + (uint32_t)tile_row * row_bytes : 0x80000000u;
