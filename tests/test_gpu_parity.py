@@ -702,6 +702,27 @@ def test_two_of_four_flag_on_4_of_8(B):
     assert seen == [1, 0]
 
 
+@pytest.mark.parametrize("B", [16, 32, 64])
+@pytest.mark.parametrize("m", [4, 8])
+def test_packed_form_of_every_n(m, B):
+    """Selection and packing for every n of a group: each n up to 4 has a packing form of its own, the others of
+    eight share one.  Rows and columns that end inside a block and inside a group, aligned rows, zeros among the
+    weights; every value, position and mask bit as the oracle has it."""
+    rng = np.random.default_rng(1000 * m + B)
+    for n in range(1, m + 1):
+        for S, K in ((B + 3, 2 * B + 5), (2 * B, 3 * B)):
+            for kind in (synth.SAL_MAG, synth.SAL_GRAD):
+                L = synth.LayerSpec("pack_%d:%d_B%d" % (n, m, B), S, K, 64, n, m, B, 0.7, kind, 0.05)
+                print(L.name, S, K, kind, flush=True)
+                Wf = rng.standard_normal((S, K)).astype(np.float32)
+                Wf[rng.random((S, K)) < 0.3] = 0.0
+                W = synth.f32_to_bf16_bits(Wf)
+                T = None if kind == synth.SAL_MAG else rng.standard_normal((S, K)).astype(np.float32)
+                sel, vals, idxw, flags = oracle_all(L, W, T)
+                layer, out = run_select_pack(L, W, T)
+                assert_select_pack_equal(L, out, sel, vals, idxw, flags)
+
+
 def test_im2col_matches_oracle():
     rng = np.random.default_rng(5)
     for (C_, H, Wd, b, kh, kw, st, pad) in [(3, 9, 8, 2, 3, 3, 1, 1), (4, 8, 8, 1, 1, 1, 2, 0), (2, 11, 11, 2, 7, 7, 2, 3),
