@@ -263,7 +263,7 @@ def run_resnet50(args):
         stats.append(dict(name=L.name, S=L.S, K=L.K, Ncol=L.Ncol, nm="%d:%d" % (L.n, L.m), B=L.B, density=round(L.density, 3),
                           k_row=dls[i].sizes.k_row, useful_flop=uf, dense_flop=2.0 * L.S * L.K * L.Ncol,
                           alg_bytes=algorithmic_bytes(L, used_cols, w_bytes, ybytes)))
-        path = crisp.conv_plan(dls[i].desc, L.conv)[0]
+        path = forward(i)         # the way that is run (a planned materialised X may give way to a fused kernel)
         d = dls[i]
         if path == "fused":
             code = crisp.crisp_conv_spmm_forced(d.desc, convs[i], d.row_ptr, d.col_idx, d.vals, d.idx_words, acts[i], Ys[i], L.Ncol, y_dtype)

@@ -319,6 +319,8 @@ CRISP_API crisp_status crisp_spmm(const crisp_layer_desc *desc, const int32_t *r
  * taps and up to four block-rows (chosen for dense multi-row layers).  Channel counts that are
  * no multiple of 64 with 64x64 blocks, even W and even Ho*Wo run in a kernel that keeps the input
  * patch of 1024 output positions in LDS.  ws, ws_bytes: reserved, ignored.
+ * With C % B == 0, W >= 4, pad < kh, up to 32 taps and enough columns a kernel takes over that stages, for a run of
+ * output positions, the input positions it touches, whatever the stride and the width.
  * Anything else returns CRISP_EUNSUPPORTED (use crisp_im2col + crisp_spmm).
  * Errors: EINVAL, ESHAPE, EALIGN, EUNSUPPORTED, EDEVICE.
  */
@@ -364,7 +366,8 @@ CRISP_API crisp_status crisp_conv_spmm_ep(const crisp_layer_desc *desc, const cr
  *   kernel_code (optional, host): receives family | shape << 8 | conv_mode << 16 | sparse << 24 of
  *          the kernel that was launched (family: CRISP_KERNEL_*; shape: the register kernels' launch
  *          shape 0..3; for the LDS-resident family bit 0 = wide strips, bit 1 = the instantiation with
- *          the larger tile capacity; else 0; conv_mode: 0 plain X, 1..4 the fused-lowering modes;
+ *          the larger tile capacity; for the staged convolutions 0 = whole output rows, 1 / 2 = a window of
+ *          input positions with 64 / 128 columns per wave; else 0; conv_mode: 0 plain X, 1..4 the fused-lowering modes;
  *          sparse: 1 when the sparse matrix-core instruction is used).  Together with (n, m, B) --
  *          B alone for the generic and 16 x 16 families and for the LDS-resident family with sparse = 0,
  *          which are not specialised by pattern -- the code names one compiled kernel.
@@ -389,7 +392,8 @@ enum {
     CRISP_SHAPE_BALANCED = 15,   /* block list dealt evenly to the waves (uneven block-rows)      */
     CRISP_SHAPE_LDS_SMF = 16,    /* block-row resident in LDS as sparse matrix-core operands      */
     CRISP_SHAPE_LDS_SMF_30 = 17, /* ... always the instantiation that holds 30 blocks             */
-    CRISP_SHAPE_XLDS = 18        /* K <= 512: a strip of X resident in LDS for all block-rows     */
+    CRISP_SHAPE_XLDS = 18,       /* K <= 512: a strip of X resident in LDS for all block-rows     */
+    CRISP_SHAPE_CONV_TILE = 19   /* fused lowering with a window of input positions in LDS        */
 };
 enum {
     CRISP_KERNEL_REG = 1, CRISP_KERNEL_GENERIC = 2, CRISP_KERNEL_LDS = 3, CRISP_KERNEL_XRES = 4,
@@ -419,7 +423,8 @@ CRISP_API crisp_status crisp_conv_spmm_forced(const crisp_layer_desc *desc, cons
  * kernel that stages the input in LDS applies, or where column pairs come from one aligned piece of
  * an input row; everything the fused entry point does not cover is materialised.
  * crisp_conv_plan (host only, pure) reports the way and the scratch bytes it needs (0 unless IM2COL).
- * crisp_conv_forward enqueues it; x_scratch may be NULL when no scratch is needed; with Y or residual
+ * crisp_conv_forward enqueues it, except that an IM2COL plan is run as FUSED where a fused kernel is known to be the
+ * faster one (the scratch is asked for all the same); x_scratch may be NULL when no scratch is needed; with Y or residual
  * row strides above 2^23 a FUSED plan is run as IM2COL (then scratch of K x round_up(Ncol, 8) is needed
  * after all); *path_taken (optional, host) receives the way taken.
  * Errors: those of the entry points named above; EBUFSIZE when the scratch is missing or too small.

@@ -21,6 +21,7 @@
 #include "spmm_xres.h"
 #include "spmm_xlds.h"
 #include "conv_patch.h"
+#include "conv_tile.h"
 #include "spmm_balanced.h"
 #include "spmm_k8.h"
 
@@ -383,6 +384,8 @@ hipError_t launch_reg_nm(const SpmmArgs& a, int B, int shape, hipStream_t st);
 template <int N, int M>
 hipError_t launch_conv_lds_nm(const SpmmArgs& a, const ConvLdsSched& s, int batch, hipStream_t st);
 template <int N, int M>
+hipError_t launch_conv_tile_nm(const SpmmArgs& a, int B, const ConvTileSched& s, hipStream_t st);
+template <int N, int M>
 hipError_t launch_conv_patch_nm(const SpmmArgs& a, const ConvPatchSched& s, int batch, hipStream_t st);
 template <int N, int M>
 hipError_t launch_balanced_nm(const SpmmArgs& a, int B, hipStream_t st);
@@ -399,6 +402,10 @@ hipError_t launch_k8_nm(const SpmmArgs& a, int B, hipStream_t st);
     template <>                                                                              \
     hipError_t launch_conv_lds_nm<N, M>(const SpmmArgs& a, const ConvLdsSched& s, int batch, hipStream_t st) { \
         return launch_conv_lds<N, M>(a, s, batch, st);                                      \
+    }                                                                                        \
+    template <>                                                                              \
+    hipError_t launch_conv_tile_nm<N, M>(const SpmmArgs& a, int B, const ConvTileSched& s, hipStream_t st) { \
+        return launch_conv_tile<N, M>(a, B, s, st);                                          \
     }                                                                                        \
     template <>                                                                              \
     hipError_t launch_conv_patch_nm<N, M>(const SpmmArgs& a, const ConvPatchSched& s, int batch, hipStream_t st) { \

@@ -393,7 +393,8 @@ static crisp_status conv_spmm_impl(const crisp_layer_desc* desc, const crisp_con
         return CRISP_EUNSUPPORTED;
     // shapes of the fused lowering that may be forced (anything else: the automatic choice)
     if (!((force_shape >= 0 && force_shape <= 3) || (force_shape >= 7 && force_shape <= 10) ||
-          force_shape == CRISP_SHAPE_CONV_LDS || force_shape == CRISP_SHAPE_CONV_PATCH || force_shape == CRISP_SHAPE_XLDS))
+          force_shape == CRISP_SHAPE_CONV_LDS || force_shape == CRISP_SHAPE_CONV_PATCH || force_shape == CRISP_SHAPE_XLDS ||
+          force_shape == CRISP_SHAPE_CONV_TILE))
         force_shape = -1;
     hipError_t e = launch_spmm(g, desc->block_density, desc->select_mode == CRISP_ROW_UNIFORM, force_shape, row_ptr, col_idx, vals,
                                idx_words, act, conv,
@@ -527,6 +528,19 @@ crisp_status crisp_conv_forward(const crisp_layer_desc* desc, const crisp_conv_d
         path = CRISP_CONV_IM2COL;
         elems = (int64_t)g.K * ((Ncol + 7) / 8 * 8);
     }
+    // a planned materialised X gives way to the kernel that needs none where that is the faster one; the plan and the
+    // scratch that goes with it stay what they are (wider row strides than the fused kernels' need them)
+    if (path == CRISP_CONV_IM2COL) {
+        if (!x_scratch || scratch_bytes < (size_t)elems * 2) {
+            if (path_taken) *path_taken = path;
+            return CRISP_EBUFSIZE;
+        }
+        if (ldy <= ((int64_t)1 << 23) && !(ep && ep->residual && ep->ldr > ((int64_t)1 << 23)) &&
+            !misaligned(x_scratch, 16) && !misaligned(row_ptr, 4) && !misaligned(col_idx, 4) &&
+            fused_lowering_covers(g, *conv, Ncol, (int64_t)conv->batch * conv->H * conv->W) &&
+            conv_tile_would_run(g, desc->block_density, *conv, Ncol, y_dtype))
+            path = CRISP_CONV_FUSED;
+    }
     if (path_taken) *path_taken = path;
     if (path == CRISP_CONV_DIRECT)
         return spmm_impl(desc, row_ptr, col_idx, vals, idx_words, act, Ncol, Ncol, CRISP_X_KN, Y, ldy, y_dtype, -1, nullptr, stream,
@@ -534,7 +548,6 @@ crisp_status crisp_conv_forward(const crisp_layer_desc* desc, const crisp_conv_d
     if (path == CRISP_CONV_FUSED)
         return conv_spmm_impl(desc, conv, row_ptr, col_idx, vals, idx_words, act, Y, ldy, y_dtype, -1, nullptr, stream, nullptr,
                               nullptr, ep);
-    if (!x_scratch || scratch_bytes < (size_t)elems * 2) return CRISP_EBUFSIZE;
     const int64_t ldx = (Ncol + 7) / 8 * 8;
     st = crisp_im2col(conv, act, x_scratch, ldx, stream);
     if (st != CRISP_OK) return st;

@@ -48,6 +48,8 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
 
 // Whether launch_spmm would run this convolution with the input patch staged in LDS (host only).
 bool conv_lds_suits(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol);
+// Whether it would run it from a window of input positions in LDS (asked before X is materialised).
+bool conv_tile_would_run(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol, int y_dtype);
 bool xlds_conv_would_run(const Geometry& g, const crisp_conv_desc& conv, int64_t Ncol);
 
 #define CRISP_BUDGET_MAX_LAYERS 64

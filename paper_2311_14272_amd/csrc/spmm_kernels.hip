@@ -393,6 +393,14 @@ template <> hipError_t launch_balanced_nm<1, 8>(const SpmmArgs&, int, hipStream_
 template <> hipError_t launch_balanced_nm<2, 8>(const SpmmArgs&, int, hipStream_t);
 template <> hipError_t launch_balanced_nm<4, 8>(const SpmmArgs&, int, hipStream_t);
 template <> hipError_t launch_balanced_nm<8, 8>(const SpmmArgs&, int, hipStream_t);
+template <> hipError_t launch_conv_tile_nm<1, 4>(const SpmmArgs&, int, const ConvTileSched&, hipStream_t);
+template <> hipError_t launch_conv_tile_nm<2, 4>(const SpmmArgs&, int, const ConvTileSched&, hipStream_t);
+template <> hipError_t launch_conv_tile_nm<3, 4>(const SpmmArgs&, int, const ConvTileSched&, hipStream_t);
+template <> hipError_t launch_conv_tile_nm<4, 4>(const SpmmArgs&, int, const ConvTileSched&, hipStream_t);
+template <> hipError_t launch_conv_tile_nm<1, 8>(const SpmmArgs&, int, const ConvTileSched&, hipStream_t);
+template <> hipError_t launch_conv_tile_nm<2, 8>(const SpmmArgs&, int, const ConvTileSched&, hipStream_t);
+template <> hipError_t launch_conv_tile_nm<4, 8>(const SpmmArgs&, int, const ConvTileSched&, hipStream_t);
+template <> hipError_t launch_conv_tile_nm<8, 8>(const SpmmArgs&, int, const ConvTileSched&, hipStream_t);
 template <> hipError_t launch_conv_lds_nm<1, 4>(const SpmmArgs&, const ConvLdsSched&, int, hipStream_t);
 template <> hipError_t launch_conv_lds_nm<2, 4>(const SpmmArgs&, const ConvLdsSched&, int, hipStream_t);
 template <> hipError_t launch_conv_lds_nm<3, 4>(const SpmmArgs&, const ConvLdsSched&, int, hipStream_t);
@@ -565,6 +573,33 @@ bool conv_lds_suits(const Geometry& g, double density_hint, const crisp_conv_des
     return (Ncol % 4) == 0 && conv_lds_plan(a, g.B, conv.kh, &cs) && conv_lds_reuses(cs, g.Sb, density_hint, conv.batch, a.Wo);
 }
 
+// Kept blocks per block-row as the descriptor states them (a hint: only speed depends on it).
+static int blocks_per_row(const Geometry& g, double density_hint) {
+    const bool hint = density_hint > 0.0 && density_hint <= 1.0;
+    const int bpr = hint ? (int)(density_hint * g.Kb + 0.5) : (g.Kb + 1) / 2;
+    return bpr < 1 ? 1 : bpr;
+}
+
+// Schedule of the convolution kernel with a window of input positions in LDS; false where it does not apply or, with
+// must_pay, is not expected to be the faster one.
+static bool conv_tile_schedule(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol, int out_bytes, bool must_pay,
+                               ConvTileSched* s) {
+    ConvShape c;
+    c.Sb = g.Sb; c.n = g.n; c.m = g.m; c.B = g.B; c.Kb = g.Kb; c.out_bytes = out_bytes;
+    c.Ncol = Ncol; c.plane = (int64_t)conv.batch * conv.H * conv.W;
+    c.C = conv.C; c.H = conv.H; c.W = conv.W; c.kh = conv.kh; c.kw = conv.kw; c.stride = conv.stride; c.pad = conv.pad;
+    c.Ho = (conv.H + 2 * conv.pad - conv.kh) / conv.stride + 1;
+    c.Wo = (conv.W + 2 * conv.pad - conv.kw) / conv.stride + 1;
+    const int bpr = blocks_per_row(g, density_hint);
+    double cost = 0.0;
+    return conv_tile_covers(c) && !(must_pay && c.kh * c.kw == 1) && conv_tile_choose(c, bpr, s, &cost) && (!must_pay || conv_tile_pays(c, bpr, cost));
+}
+
+bool conv_tile_would_run(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol, int y_dtype) {
+    ConvTileSched s;
+    return conv_tile_schedule(g, density_hint, conv, Ncol, y_dtype == CRISP_Y_BF16 ? 2 : 4, true, &s);
+}
+
 hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows, int force_shape, const int32_t* row_ptr,
                        const int32_t* col_idx, const uint16_t* vals, const uint32_t* idxw, const uint16_t* X,
                        const crisp_conv_desc* conv, int64_t Ncol, int64_t ldx, void* Y, int64_t ldy, int y_dtype,
@@ -615,6 +650,23 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
         }
     }
     if (g.B == 16) { report(CRISP_KERNEL_B16, 0, 0, 0); return launch_b16(a, st); }
+    // convolution from a window of input positions in LDS (forced shape 19)
+    ConvTileSched ts;
+    if (conv && (force_shape == CRISP_SHAPE_CONV_TILE || force_shape < 0) && ld_wide <= ((int64_t)1 << 23) &&
+        conv_tile_schedule(g, density_hint, *conv, Ncol, a.y_bf16 ? 2 : 4, force_shape < 0, &ts)) {
+        report(CRISP_KERNEL_CONV_LDS, ts.NC2, a.conv_mode, g.n <= 2);
+        switch (g.n * 16 + g.m) {
+            case 1 * 16 + 4: return launch_conv_tile_nm<1, 4>(a, g.B, ts, st);
+            case 2 * 16 + 4: return launch_conv_tile_nm<2, 4>(a, g.B, ts, st);
+            case 3 * 16 + 4: return launch_conv_tile_nm<3, 4>(a, g.B, ts, st);
+            case 4 * 16 + 4: return launch_conv_tile_nm<4, 4>(a, g.B, ts, st);
+            case 1 * 16 + 8: return launch_conv_tile_nm<1, 8>(a, g.B, ts, st);
+            case 2 * 16 + 8: return launch_conv_tile_nm<2, 8>(a, g.B, ts, st);
+            case 4 * 16 + 8: return launch_conv_tile_nm<4, 8>(a, g.B, ts, st);
+            case 8 * 16 + 8: return launch_conv_tile_nm<8, 8>(a, g.B, ts, st);
+            default: break;
+        }
+    }
     // convolution with the input patch staged in LDS (forced shape 12)
     ConvLdsSched cs;
     const bool conv_lds_wanted = force_shape == 12 || force_shape < 0;
@@ -653,11 +705,8 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
             default: break;
         }
     }
-    // LDS-resident block-rows (forced shapes 5 = narrow strips, 6 = wide strips)
-    // kept blocks per block-row as the descriptor states them (a hint: only speed depends on it)
     const bool hint = density_hint > 0.0 && density_hint <= 1.0;
-    int bpr = hint ? (int)(density_hint * g.Kb + 0.5) : (g.Kb + 1) / 2;
-    if (bpr < 1) bpr = 1;
+    const int bpr = blocks_per_row(g, density_hint);
     // LDS-resident block-rows (forced shapes 5 = narrow strips, 6 = wide strips)
     const bool lds_ok = !conv && (g.K % 16) == 0 && (Ncol % 4) == 0 && ld_wide <= ((int64_t)1 << 23);
     // (reported shape of this family: bit 0 = wide strips, bit 1 = the instantiation with the larger tile capacity
