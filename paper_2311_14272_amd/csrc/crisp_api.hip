@@ -173,7 +173,7 @@ static crisp_status select_pack_run(int32_t n_layers, const crisp_layer_desc* de
                                 bufs[i].vals, bufs[i].idx_words, bufs[i].flags, (hipStream_t)stream);
             continue;
         }
-        // this layer and the later ones of the same kernel instantiation, CRISP_SELECT_BATCH per launch pair
+        // this layer and the later ones of the same block size and saliency kind, CRISP_SELECT_BATCH per launch pair
         Geometry gg[CRISP_SELECT_BATCH];
         SelPackPtrs pp[CRISP_SELECT_BATCH];
         int cnt = 0;
@@ -181,8 +181,7 @@ static crisp_status select_pack_run(int32_t n_layers, const crisp_layer_desc* de
         for (int j = i; j < n_layers && cnt < CRISP_SELECT_BATCH; ++j) {
             const Geometry& h = geo[j];
             if (done[j] || !select_pack_fusable(h, descs[j].select_mode)) continue;
-            if (h.B != g.B || h.m != g.m || descs[j].sal_kind != descs[i].sal_kind || (h.K % h.B == 0) != (g.K % g.B == 0))
-                continue;
+            if (h.B != g.B || descs[j].sal_kind != descs[i].sal_kind) continue;
             if (blocks + (int64_t)h.Sb * h.Kb > (1 << 30)) break;
             blocks += (int64_t)h.Sb * h.Kb;
             const size_t sb = ((size_t)h.Sb * h.Kb * sizeof(double) + 15) / 16 * 16;

@@ -13,40 +13,65 @@ namespace crisp {
 // values left to right in fp64 and lane 0 adds the row sums top to bottom: that summation order
 // is part of the definition of the block score (a tree reduction would round differently;
 // adding +0.0 for a pruned element leaves the non-negative running sum unchanged bit for bit).
-// VEC: row segments are 16-byte aligned and lie wholly inside the matrix (K % B == 0).
 // PACK: while the block's weights and keep bits are in registers, its packed form (compressed
 // values, position stream, 2-of-4 violation) is also written, to a staging area indexed by the
 // block's place in the grid; whether the block is kept is only known after the block choice,
 // which then just copies the kept blocks' packed forms to their final place (topk_gather_kernel).
-// Up to SEL_BATCH layers of equal (B, m, saliency kind, alignment class) share one launch: a
-// model's layers have block grids of a few dozen to a few hundred workgroups each, far too few to
-// fill 256 compute units one layer at a time.  Workgroup ids are mapped to (layer, block) through
-// the prefix sums in `first`.
+// Up to CAP layers of equal (B, saliency kind) share one launch: a model's layers have block grids of a few dozen to a few
+// hundred workgroups each, far too few to fill 256 compute units one layer at a time, and a launch has a ramp and a last
+// wave of its own (the 53 layers of ResNet-50: two launches in place of eight, one pair per pattern width and alignment,
+// 82 -> 47 us on the GPU).  Workgroup ids are mapped to (layer, block) through the prefix sums in `first`.
+template <class BATCH>
+__device__ __forceinline__ int layer_of(const BATCH& bt, int id) {
+    constexpr int CAP = sizeof(bt.first) / 4 - 1;
+    if constexpr (CAP == 1) return 0;
+    static_assert(CAP <= 64, "one lane per layer");
+    const int lane = threadIdx.x & 63;
+    return __popcll(__ballot(lane > 0 && lane < bt.n && id >= bt.first[lane]));
+}
+
+// Saliency, N:M choice and (PACK) packed form of one lane's columns; returns the keep bits.
 template <int B, int M, int KIND, bool VEC, bool PACK>
-__global__ __launch_bounds__(B * (B / 16)) void score_select_kernel(SelBatch bt) {
-    int li = 0;
-#pragma unroll
-    for (int i = 1; i < SEL_BATCH; ++i) li += (i < bt.n && (int)blockIdx.x >= bt.first[i]);
-    const SelLayer& sa = bt.L[li];
-    const int S = sa.S, K = sa.K, n = sa.n, Kb = sa.Kb, mwpr = sa.mwpr;
-    const uint16_t* __restrict__ W = sa.W;
-    const float* __restrict__ TG = sa.TG;
+__device__ __forceinline__ uint32_t score_lane(const ScoreLayer& sa, const SelStage& stg, size_t blk, int r, int s, int c0, int k0,
+                                               float* kept_dst, uint32_t* pos_row, int wmax, int* viol) {
+    constexpr bool NEEDW = PACK || KIND != CRISP_SAL_GIVEN;
+    const int len = (s < sa.S) ? min(LANE_COLS, sa.K - k0) : 0;   // columns of this lane that exist (may be <= 0)
+    LaneRaw raw;
+    lane_load<KIND, VEC, NEEDW>(raw, sa.W, sa.TG, (size_t)min(s, sa.S - 1) * sa.K, k0, sa.K);
+    const uint32_t bits = lane_select<M, KIND, NEEDW, true>(raw, sa.n, len, kept_dst);
+    if constexpr (PACK) {
+        // packed form of the lane's groups, to the block's staging area
+        const int slot0 = (c0 / M) * sa.n;
+        uint16_t* sv = reinterpret_cast<uint16_t*>(sa.stage + stg.vals_off) + (blk * B + r) * stg.slots + slot0;
+        uint16_t w[LANE_COLS];
+        lane_weights(raw, len, w);
+        if (lane_pack<M>(w, bits, sa.n, stg.wbits, s >= sa.S, k0, sa.K, sv, pos_row, slot0, wmax)) *viol = 1;
+    }
+    return bits;
+}
+
+template <int B, int KIND, bool PACK, int CAP>
+__global__ __launch_bounds__(B * (B / 16)) void score_select_kernel(SelBatch<ScoreLayer, CAP> bt) {
+    const int li = __builtin_amdgcn_readfirstlane(layer_of(bt, (int)blockIdx.x));
+    const ScoreLayer& sa = bt.L[li];
+    const int local = (int)blockIdx.x - bt.first[li];
+    const int S = sa.S, K = sa.K;
+    const int Kb = (K + B - 1) / B, mwpr = (K + 31) / 32;
     uint32_t* __restrict__ nm_mask = sa.nm_mask;
-    double* __restrict__ score = sa.score;
-    constexpr int CPT = LANE_COLS;   // columns per lane
-    constexpr int Q = B / CPT;       // lanes per block row (1, 2 or 4)
-    constexpr int LDT = B + 4;       // padded LDS row stride in floats (keeps 16-byte alignment)
+    const SelStage stg = sel_stage(B, sa.n, sa.m, (size_t)((S + B - 1) / B) * Kb);
+    constexpr int Q = B / LANE_COLS;  // lanes per block row (1, 2 or 4)
+    constexpr int LDT = B + 4;        // padded LDS row stride in floats (keeps 16-byte alignment)
     constexpr int WMAX = (B * 3 + 31) / 32;   // upper bound of position words per block row
     constexpr int NTHR = B * (B / 16);
     __shared__ __attribute__((aligned(16))) float tkept[B * LDT];
     __shared__ double rowsum[B];
     __shared__ uint32_t pos_lds[PACK ? B * WMAX : 1];
     __shared__ int viol_lds;
-    const int local = (int)blockIdx.x - bt.first[li];
     const int bi = local / Kb, bj = local - bi * Kb;
+    const size_t blk = (size_t)bi * Kb + bj;
     const int r = threadIdx.x / Q, q = threadIdx.x % Q;
     const int s = bi * B + r;
-    const int c0 = q * CPT;                      // first column of this lane inside the block
+    const int c0 = q * LANE_COLS;                // first column of this lane inside the block
     const int k0 = bj * B + c0;
     if constexpr (PACK) {
         for (int e = threadIdx.x; e < B * WMAX; e += NTHR) pos_lds[e] = 0u;
@@ -56,22 +81,16 @@ __global__ __launch_bounds__(B * (B / 16)) void score_select_kernel(SelBatch bt)
         }
         __syncthreads();
     }
+    float* kept_dst = &tkept[r * LDT + c0];
+    uint32_t* pos_row = pos_lds + (PACK ? r * WMAX : 0);
     uint32_t bits;
-    {
-        constexpr bool NEEDW = PACK || KIND != CRISP_SAL_GIVEN;
-        const int len = (s < S) ? min(CPT, K - k0) : 0;   // columns of this lane that exist (may be <= 0)
-        LaneRaw raw;
-        lane_load<KIND, VEC, NEEDW>(raw, W, TG, (size_t)min(s, S - 1) * K, k0, K);
-        bits = lane_select<M, KIND, NEEDW, true>(raw, n, len, &tkept[r * LDT + c0]);
-        if constexpr (PACK) {
-            // packed form of the lane's groups, to the staging area of block (bi, bj)
-            const size_t blk = (size_t)bi * Kb + bj;
-            const int slot0 = (c0 / M) * n;
-            uint16_t* sv = sa.st_vals + (blk * B + r) * sa.slots + slot0;
-            uint16_t w[CPT];
-            lane_weights(raw, len, w);
-            if (lane_pack<M>(w, bits, n, sa.wbits, s >= S, k0, K, sv, pos_lds + r * WMAX, slot0, WMAX)) viol_lds = 1;
-        }
+    const bool vec = K % B == 0;                 // row segments are 16-byte aligned and lie wholly inside the matrix
+    if (sa.m == 4) {
+        bits = vec ? score_lane<B, 4, KIND, true, PACK>(sa, stg, blk, r, s, c0, k0, kept_dst, pos_row, WMAX, &viol_lds)
+                   : score_lane<B, 4, KIND, false, PACK>(sa, stg, blk, r, s, c0, k0, kept_dst, pos_row, WMAX, &viol_lds);
+    } else {
+        bits = vec ? score_lane<B, 8, KIND, true, PACK>(sa, stg, blk, r, s, c0, k0, kept_dst, pos_row, WMAX, &viol_lds)
+                   : score_lane<B, 8, KIND, false, PACK>(sa, stg, blk, r, s, c0, k0, kept_dst, pos_row, WMAX, &viol_lds);
     }
     // mask: the Q lanes of a row hold 16 bits each; pairs of lanes form one 32-bit word
     if (Q >= 2) {
@@ -103,18 +122,21 @@ __global__ __launch_bounds__(B * (B / 16)) void score_select_kernel(SelBatch bt)
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        double part[B];
-#pragma unroll
-        for (int i = 0; i < B; ++i) part[i] = rowsum[i];
         double total = 0.0;
 #pragma unroll
-        for (int i = 0; i < B; ++i) total = __dadd_rn(total, part[i]);
-        score[(size_t)bi * Kb + bj] = total;
-        if constexpr (PACK) sa.st_viol[(size_t)bi * Kb + bj] = viol_lds;
+        for (int i0 = 0; i0 < B; i0 += 16) {     // sixteen at a time: requested together, in few registers
+            double part[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) part[i] = rowsum[i0 + i];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) total = __dadd_rn(total, part[i]);
+        }
+        sa.score[blk] = total;
+        if constexpr (PACK) reinterpret_cast<int32_t*>(sa.stage)[blk] = viol_lds;
     }
     if constexpr (PACK) {
-        uint32_t* dst = sa.st_idxw + ((size_t)bi * Kb + bj) * B * sa.wpr;
-        for (int e = threadIdx.x; e < B * sa.wpr; e += NTHR) dst[e] = pos_lds[(e / sa.wpr) * WMAX + e % sa.wpr];
+        uint32_t* dst = reinterpret_cast<uint32_t*>(sa.stage + stg.idxw_off) + blk * B * stg.wpr;
+        for (int e = threadIdx.x; e < B * stg.wpr; e += NTHR) dst[e] = pos_lds[(e / stg.wpr) * WMAX + e % stg.wpr];
     }
 }
 
@@ -200,47 +222,30 @@ __global__ __launch_bounds__(1024) void block_topk_layer_kernel(int Sb, int Kb, 
     for (int bi = wave; bi < Sb; bi += 16) wave_compact(kept + bi * Kb, Kb, col_idx + rowcnt[bi], lane);
 }
 
-// One launch of the scoring kernel for a batch whose layers share (B, m, kind, vec).
-template <int KIND, bool PACK>
-static void launch_score_batch(int B, int m, bool vec, const SelBatch& bt, hipStream_t st) {
+// One launch of the scoring kernel for a batch whose layers share (B, kind).
+template <int KIND, bool PACK, int CAP>
+static void launch_score_batch(int B, const SelBatch<ScoreLayer, CAP>& bt, hipStream_t st) {
     const unsigned grid = (unsigned)bt.first[bt.n];
     if (grid == 0) return;
-#define CRISP_SCORE_CASE(BB, MM)                                                                       \
-    if (vec) score_select_kernel<BB, MM, KIND, true, PACK><<<grid, BB * (BB / 16), 0, st>>>(bt);          \
-    else score_select_kernel<BB, MM, KIND, false, PACK><<<grid, BB * (BB / 16), 0, st>>>(bt);
-    switch (B * 16 + m) {
-        case 64 * 16 + 4: CRISP_SCORE_CASE(64, 4) break;
-        case 64 * 16 + 8: CRISP_SCORE_CASE(64, 8) break;
-        case 32 * 16 + 4: CRISP_SCORE_CASE(32, 4) break;
-        case 32 * 16 + 8: CRISP_SCORE_CASE(32, 8) break;
-        case 16 * 16 + 4: CRISP_SCORE_CASE(16, 4) break;
-        default: CRISP_SCORE_CASE(16, 8) break;
-    }
-#undef CRISP_SCORE_CASE
+    if (B == 64) score_select_kernel<64, KIND, PACK, CAP><<<grid, 256, 0, st>>>(bt);
+    else if (B == 32) score_select_kernel<32, KIND, PACK, CAP><<<grid, 64, 0, st>>>(bt);
+    else score_select_kernel<16, KIND, PACK, CAP><<<grid, 16, 0, st>>>(bt);
 }
 
-template <bool PACK>
-static void launch_score_kind(int sal_kind, int B, int m, bool vec, const SelBatch& bt, hipStream_t st) {
-    if (sal_kind == CRISP_SAL_GIVEN) launch_score_batch<CRISP_SAL_GIVEN, PACK>(B, m, vec, bt, st);
-    else if (sal_kind == CRISP_SAL_GRAD) launch_score_batch<CRISP_SAL_GRAD, PACK>(B, m, vec, bt, st);
-    else launch_score_batch<CRISP_SAL_MAG, PACK>(B, m, vec, bt, st);
-}
-
-static SelLayer sel_layer_of(const Geometry& g, const uint16_t* W, const float* TG, uint32_t* nm_mask, double* score) {
-    SelLayer L = {};
-    L.S = g.S; L.K = g.K; L.n = g.n; L.Kb = g.Kb; L.Sb = g.Sb; L.mwpr = g.mwpr; L.k_row = g.k_row;
-    L.wbits = g.w; L.slots = g.slots; L.wpr = g.wpr;
-    L.W = W; L.TG = TG; L.nm_mask = nm_mask; L.score = score;
-    return L;
+template <bool PACK, int CAP>
+static void launch_score_kind(int sal_kind, int B, const SelBatch<ScoreLayer, CAP>& bt, hipStream_t st) {
+    if (sal_kind == CRISP_SAL_GIVEN) launch_score_batch<CRISP_SAL_GIVEN, PACK>(B, bt, st);
+    else if (sal_kind == CRISP_SAL_GRAD) launch_score_batch<CRISP_SAL_GRAD, PACK>(B, bt, st);
+    else launch_score_batch<CRISP_SAL_MAG, PACK>(B, bt, st);
 }
 
 hipError_t launch_select(const Geometry& g, int sal_kind, int select_mode, const uint16_t* W, const float* TG,
                          uint32_t* nm_mask, int32_t* row_ptr, int32_t* col_idx, double* score, hipStream_t st) {
-    SelBatch bt = {};
+    SelBatch<ScoreLayer, 1> bt = {};
     bt.n = 1;
-    bt.L[0] = sel_layer_of(g, W, TG, nm_mask, score);
+    bt.L[0] = ScoreLayer{W, TG, nm_mask, score, nullptr, nullptr, g.S, g.K, g.n, g.m};
     bt.first[1] = g.Sb * g.Kb;
-    launch_score_kind<false>(sal_kind, g.B, g.m, g.K % g.B == 0, bt, st);
+    launch_score_kind<false>(sal_kind, g.B, bt, st);
     if (select_mode == CRISP_ROW_UNIFORM)
         block_topk_rows_kernel<<<g.Sb, 256, 0, st>>>(g.Sb, g.Kb, g.k_row, score, row_ptr, col_idx);
     else
@@ -254,18 +259,19 @@ hipError_t launch_select(const Geometry& g, int sal_kind, int select_mode, const
 // less than a launch), takes the t-th kept column in ascending order and copies that block's
 // packed form from the staging area to its final place.  Results are identical to
 // crisp_select_mask followed by crisp_pack.
-__global__ __launch_bounds__(256) void topk_gather_kernel(SelBatch bt, int B) {
+template <int CAP>
+__global__ __launch_bounds__(256) void topk_gather_kernel(SelBatch<GatherLayer, CAP> bt, int B) {
     __shared__ double sc[512];
     __shared__ uint8_t kept[512];
     __shared__ int sel;
-    int li = 0;
-#pragma unroll
-    for (int i = 1; i < SEL_BATCH; ++i) li += (i < bt.n && (int)blockIdx.x >= bt.firstk[i]);
-    const SelLayer& L = bt.L[li];
-    const int local = (int)blockIdx.x - bt.firstk[li];
-    const int Kb = L.Kb, k_row = L.k_row, Sb = L.Sb;
+    const int li = __builtin_amdgcn_readfirstlane(layer_of(bt, (int)blockIdx.x));
+    const GatherLayer& L = bt.L[li];
+    const int local = (int)blockIdx.x - bt.first[li];
+    const int Kb = (int)(L.Kb_k_nm & 0xFFFu), k_row = (int)(L.Kb_k_nm >> 12 & 0xFFFu), Sb = L.Sb;
+    const int n = (int)(L.Kb_k_nm >> 24 & 0xFu), m = (int)(L.Kb_k_nm >> 28);
+    const SelStage stg = sel_stage(B, n, m, (size_t)Sb * Kb);
     const int bi = local / k_row, t = local - bi * k_row, tid = threadIdx.x;
-    const int vbytes = B * L.slots * 2, ibytes = B * L.wpr * 4;
+    const int vbytes = B * stg.slots * 2, ibytes = B * stg.wpr * 4;
     for (int j = tid; j < Kb; j += 256) sc[j] = L.score[(size_t)bi * Kb + j];
     __syncthreads();
     for (int j = tid; j < Kb; j += 256) {
@@ -285,10 +291,10 @@ __global__ __launch_bounds__(256) void topk_gather_kernel(SelBatch bt, int B) {
     __syncthreads();
     const int bj = sel;
     const size_t src = (size_t)bi * Kb + bj, dst = (size_t)bi * k_row + t;
-    const u32x4* sv = reinterpret_cast<const u32x4*>(reinterpret_cast<const unsigned char*>(L.st_vals) + src * vbytes);
+    const u32x4* sv = reinterpret_cast<const u32x4*>(L.stage + stg.vals_off + src * vbytes);
     u32x4* dv = reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(L.vals) + dst * vbytes);
     for (int e = tid; e < vbytes / 16; e += 256) dv[e] = sv[e];
-    const u32x4* si = reinterpret_cast<const u32x4*>(reinterpret_cast<const unsigned char*>(L.st_idxw) + src * ibytes);
+    const u32x4* si = reinterpret_cast<const u32x4*>(L.stage + stg.idxw_off + src * ibytes);
     u32x4* di = reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(L.idxw) + dst * ibytes);
     for (int e = tid; e < ibytes / 16; e += 256) di[e] = si[e];
     if (tid == 0) {
@@ -297,7 +303,8 @@ __global__ __launch_bounds__(256) void topk_gather_kernel(SelBatch bt, int B) {
             L.row_ptr[bi] = bi * k_row;
             if (bi == Sb - 1) L.row_ptr[Sb] = Sb * k_row;
         }
-        if (L.clear_flag && L.st_viol[src] && L.flags[0] != 0) atomicAnd(L.flags, 0);
+        // (n <= 2 can never put three kept elements into an aligned group of four)
+        if (n > 2 && reinterpret_cast<const int32_t*>(L.stage)[src] && L.flags[0] != 0) atomicAnd(L.flags, 0);
     }
 }
 
@@ -307,34 +314,32 @@ bool select_pack_fusable(const Geometry& g, int select_mode) {
 
 size_t select_pack_stage_bytes(const Geometry& g) {
     const size_t blocks = (size_t)g.Sb * g.Kb;
-    const size_t viol = (blocks * sizeof(int32_t) + 15) / 16 * 16;
-    return viol + blocks * g.B * g.slots * 2 + blocks * g.B * g.wpr * 4;
+    return sel_stage(g.B, g.n, g.m, blocks).idxw_off + blocks * g.B * g.wpr * 4;
 }
 
-// Fused selection + packing of up to SEL_BATCH layers that share (B, m, saliency kind, alignment
-// class) in two launches.  stage[i]: select_pack_stage_bytes(g[i]) bytes, 16-byte aligned.
-hipError_t launch_select_pack_batch(int n, const Geometry* g, int sal_kind, const SelPackPtrs* pp, hipStream_t st) {
-    SelBatch bt = {};
-    bt.n = n;
+template <int CAP>
+static hipError_t launch_select_pack(int n, const Geometry* g, int sal_kind, const SelPackPtrs* pp, hipStream_t st) {
+    SelBatch<ScoreLayer, CAP> sb;
+    SelBatch<GatherLayer, CAP> gb;
+    sb.n = gb.n = n;
+    sb.first[0] = gb.first[0] = 0;
     for (int i = 0; i < n; ++i) {
-        const size_t blocks = (size_t)g[i].Sb * g[i].Kb;
-        unsigned char* base = static_cast<unsigned char*>(pp[i].stage);
-        SelLayer L = sel_layer_of(g[i], pp[i].W, pp[i].TG, pp[i].nm_mask, pp[i].score);
-        L.st_viol = reinterpret_cast<int32_t*>(base);
-        base += (blocks * sizeof(int32_t) + 15) / 16 * 16;
-        L.st_vals = reinterpret_cast<uint16_t*>(base);
-        base += blocks * g[i].B * g[i].slots * 2;
-        L.st_idxw = reinterpret_cast<uint32_t*>(base);
-        L.flags = pp[i].flags; L.row_ptr = pp[i].row_ptr; L.col_idx = pp[i].col_idx; L.vals = pp[i].vals; L.idxw = pp[i].idxw;
-        // n <= 2 can never put three kept elements into an aligned group of four
-        L.clear_flag = g[i].n > 2;
-        bt.L[i] = L;
-        bt.first[i + 1] = bt.first[i] + g[i].Sb * g[i].Kb;
-        bt.firstk[i + 1] = bt.firstk[i] + g[i].nk;
+        unsigned char* stage = static_cast<unsigned char*>(pp[i].stage);
+        sb.L[i] = ScoreLayer{pp[i].W, pp[i].TG, pp[i].nm_mask, pp[i].score, stage, pp[i].flags, g[i].S, g[i].K, g[i].n, g[i].m};
+        gb.L[i] = GatherLayer{pp[i].score, stage, pp[i].vals, pp[i].idxw, pp[i].col_idx, pp[i].row_ptr, pp[i].flags, g[i].Sb,
+                              (uint32_t)g[i].Kb | (uint32_t)g[i].k_row << 12 | (uint32_t)g[i].n << 24 | (uint32_t)g[i].m << 28};
+        sb.first[i + 1] = sb.first[i] + g[i].Sb * g[i].Kb;
+        gb.first[i + 1] = gb.first[i] + g[i].nk;
     }
-    launch_score_kind<true>(sal_kind, g[0].B, g[0].m, g[0].K % g[0].B == 0, bt, st);
-    if (bt.firstk[n] > 0) topk_gather_kernel<<<(unsigned)bt.firstk[n], 256, 0, st>>>(bt, g[0].B);
+    launch_score_kind<true>(sal_kind, g[0].B, sb, st);
+    if (gb.first[n] > 0) topk_gather_kernel<CAP><<<(unsigned)gb.first[n], 256, 0, st>>>(gb, g[0].B);
     return hipGetLastError();
+}
+
+// Fused selection + packing of up to CRISP_SELECT_BATCH layers that share (B, saliency kind) in two launches.
+// stage: select_pack_stage_bytes(g[i]) bytes, 16-byte aligned.
+hipError_t launch_select_pack_batch(int n, const Geometry* g, int sal_kind, const SelPackPtrs* pp, hipStream_t st) {
+    return n == 1 ? launch_select_pack<1>(n, g, sal_kind, pp, st) : launch_select_pack<CRISP_SELECT_BATCH>(n, g, sal_kind, pp, st);
 }
 
 }  // namespace crisp

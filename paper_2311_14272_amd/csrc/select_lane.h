@@ -9,30 +9,52 @@ namespace crisp {
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-#define SEL_BATCH CRISP_SELECT_BATCH
-// One layer of a batched selection launch.
-struct SelLayer {
-    int S, K, n, Kb, Sb, mwpr, k_row, clear_flag;
-    int wbits, slots, wpr, pad_;  // bits per position, packed slots and position words per block row
+// The layers of a batched selection launch travel in the kernel arguments (4 KB): 64 bytes a layer in either launch, what
+// follows from the sizes is formed on the device.  CAP: 1 for a single layer, whose launch then carries 80 bytes.
+struct ScoreLayer {
     const uint16_t* W;
     const float* TG;
     uint32_t* nm_mask;
     double* score;
-    uint16_t* st_vals;            // staging [Sb*Kb][B][slots]
-    uint32_t* st_idxw;            // staging [Sb*Kb][B][wpr]
-    int32_t* st_viol;             // staging [Sb*Kb]: an aligned group of four holds more than two kept
-    int32_t* flags;               // the layer's flags
-    int32_t* row_ptr;
-    int32_t* col_idx;
+    unsigned char* stage;         // staging area of the packed forms (PACK), see SelStage
+    int32_t* flags;               // the layer's flags (PACK)
+    int S, K;
+    int n, m;
+};
+struct GatherLayer {
+    const double* score;
+    const unsigned char* stage;
     uint16_t* vals;
     uint32_t* idxw;
+    int32_t* col_idx;
+    int32_t* row_ptr;
+    int32_t* flags;
+    int Sb;
+    uint32_t Kb_k_nm;             // block columns | kept blocks per block-row << 12 | n << 24 | m << 28
 };
+static_assert(sizeof(ScoreLayer) == 64 && sizeof(GatherLayer) == 64, "both batches fit the kernel arguments");
+template <class LAYER, int CAP>
 struct SelBatch {
     int n;
-    int first[SEL_BATCH + 1];     // first workgroup of each layer in the scoring launch
-    int firstk[SEL_BATCH + 1];    // first workgroup of each layer in the gather launch (kept blocks)
-    SelLayer L[SEL_BATCH];
+    int first[CAP + 1];           // first workgroup of each layer
+    LAYER L[CAP];
 };
+
+// Staging area of a layer's packed forms, one per block of the grid: [blocks] 2-of-4 violation (an aligned group of four
+// holds more than two kept), padded to 16 bytes; [blocks][B][slots] values; [blocks][B][wpr] position words.
+struct SelStage {
+    int slots, wpr, wbits;        // packed slots and position words per block row, bits per position
+    size_t vals_off, idxw_off;
+};
+__host__ __device__ __forceinline__ SelStage sel_stage(int B, int n, int m, size_t blocks) {
+    SelStage s;
+    s.slots = B / m * n;
+    s.wbits = m == 4 ? 2 : 3;
+    s.wpr = (s.slots * s.wbits + 31) / 32;
+    s.vals_off = (blocks * 4 + 15) / 16 * 16;
+    s.idxw_off = s.vals_off + blocks * B * s.slots * 2;
+    return s;
+}
 
 constexpr int LANE_COLS = 16;     // columns per lane
 
