@@ -25,7 +25,11 @@ constexpr uint32_t CONV_TILE_IDLE = 0x80000000u;
 
 __device__ __forceinline__ int divide(int n, DivBy d) { return d.m ? (int)(__umulhi((uint32_t)n, d.m) >> d.shift) : n; }
 
-template <int N, int M, int B, int NC2, bool SMF>
+// SPAN: channel counts that are no multiple of the block edge (but of eight): a block column holds K-rows of several taps.
+// Every octet of K-rows is still eight channels of one tap; a table in LDS says where it lies in the chunk (or that it is
+// not there: zeros), and each 16-deep step forms its own addresses from it.  A block is walked in every chunk it has a
+// part in.
+template <int N, int M, int B, int NC2, bool SMF, bool SPAN>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NC2 == 2 ? 2 : 3, NC2 == 2 ? 2 : 4)))
 void conv_tile_kernel(SpmmArgs p, ConvTileSched sc) {
     typedef Fmt<N, M, B> F;
@@ -64,26 +68,30 @@ void conv_tile_kernel(SpmmArgs p, ConvTileSched sc) {
     uint32_t* lists = reinterpret_cast<uint32_t*>(lds + zero_row + 128);
     uint32_t* list = lists + r_in * sc.list_cap * 2;
     int* run_end = reinterpret_cast<int*>(lists + sc.RG * sc.list_cap * 2) + r_in * sc.chunks;
+    // SPAN: octet of K-rows -> byte offset of its place | tap << 20 | odd shift << 30 (tap 31, which no lane has: elsewhere)
+    uint32_t* octets = lists + sc.RG * (sc.list_cap * 2 + sc.chunks);
 
     // ---- staging: a unit is 16 channels x 128 positions; a lane takes four neighbouring positions of eight channels
     // (its half of the sixteen), 8 bytes per request, transposes them with v_perm_b32 and writes the eight channels of
     // each position with one 16-byte write.  The last lane of the window starts four positions before its end. --------
     const int pieces = (npos + 127) >> 7;
     const uint32_t pieces_inv = (65536u + (uint32_t)pieces - 1u) / (uint32_t)pieces;
-    auto units_of = [&](int q) __attribute__((always_inline)) { return (min(sc.CC, p.C - q * sc.CC) >> 4) * pieces; };
+    auto units_of = [&](int q) __attribute__((always_inline)) { return ((min(sc.CC, p.C - q * sc.CC) + (SPAN ? 8 : 0)) >> 4) * pieces; };
     auto request = [&](int q, int u, u32x2 (&v)[8]) __attribute__((always_inline)) {
         const uint32_t plane_bytes = (uint32_t)p.plane * 2u;
         u = min(u, units_of(q) - 1);
         const int g = (int)(((uint32_t)u * pieces_inv) >> 16), pc = u - g * pieces;
         const rsrc_t r = make_rsrc(p.act + (int64_t)(q * sc.CC + g * 16) * p.plane + lo);
-        const uint32_t off = (uint32_t)hh * 8u * plane_bytes + (uint32_t)min(pc * 128 + jj * 4, npos - 4) * 2u;
+        // (SPAN: an odd number of octets leaves the upper half of the last unit without channels: it re-reads the lower's)
+        const uint32_t upper = SPAN && q * sc.CC + g * 16 + 8 >= p.C ? 0u : (uint32_t)hh;
+        const uint32_t off = upper * 8u * plane_bytes + (uint32_t)min(pc * 128 + jj * 4, npos - 4) * 2u;
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] = buf_load_x<2>(r, off, (uint32_t)i * plane_bytes);
     };
     auto deposit = [&](int q, int u, const u32x2 (&v)[8]) __attribute__((always_inline)) {
         if (u >= units_of(q)) return;
         const int g = (int)(((uint32_t)u * pieces_inv) >> 16), pc = u - g * pieces;
-        if (pc * 128 + jj * 4 >= npos) return;
+        if (pc * 128 + jj * 4 >= npos || (SPAN && q * sc.CC + g * 16 + hh * 8 >= p.C)) return;
         const int first = min(pc * 128 + jj * 4, npos - 4);
         const uint32_t at = (uint32_t)((g * 16 + hh * 8) * 2);
 #pragma unroll
@@ -131,8 +139,8 @@ void conv_tile_kernel(SpmmArgs p, ConvTileSched sc) {
             }
             const int ih = oh * p.stride - p.pad, iw = ow * p.stride - p.pad;
             const int pos = (img * p.H + ih) * p.W + iw - lo;
-            base_even[2 * c2 + c] = (uint32_t)(((pos & 1) * sc.HP + (pos >> 1)) * sc.pitch + hh * 16);
-            base_odd[2 * c2 + c] = (uint32_t)((((pos + 1) & 1) * sc.HP + ((pos + 1) >> 1)) * sc.pitch + hh * 16);
+            base_even[2 * c2 + c] = (uint32_t)(((pos & 1) * sc.HP + (pos >> 1)) * sc.pitch + (SPAN ? 0 : hh * 16));
+            base_odd[2 * c2 + c] = (uint32_t)((((pos + 1) & 1) * sc.HP + ((pos + 1) >> 1)) * sc.pitch + (SPAN ? 0 : hh * 16));
             uint32_t cols_in = 0, taps_in = 0;
             for (int b = 0; b < p.kw; ++b) cols_in |= ((unsigned)(iw + b) < (unsigned)p.W ? 1u : 0u) << b;
             for (int a = 0; a < sc.kh; ++a) taps_in |= ((unsigned)(ih + a) < (unsigned)p.H ? cols_in : 0u) << (a * p.kw);
@@ -165,15 +173,24 @@ void conv_tile_kernel(SpmmArgs p, ConvTileSched sc) {
                 const int e = e0 + lane;
                 const int bj = p.col_idx[t_begin + min(e, cnt - 1)];
                 const int tap = (int)(((float)bj + 0.5f) * inv_CB), cb = bj - tap * sc.CB;
-                const int mine = (int)(((float)cb + 0.5f) * inv_CBC);
-                const bool here = e < cnt && mine == q;
+                bool here = e < cnt;
+                if constexpr (SPAN) {              // any octet of the block's rows with channels of this chunk
+                    bool any = sc.chunks == 1;
+                    for (int o = 0; o < B / 8 && !__all(any); ++o) {
+                        const int k = bj * B + o * 8, c = k - (int)(((float)k + 0.5f) * p.inv_C) * p.C;
+                        any = any || (k < p.K && c >= q * sc.CC && c < (q + 1) * sc.CC);
+                    }
+                    here = here && any;
+                } else {
+                    here = here && (int)(((float)cb + 0.5f) * inv_CBC) == q;
+                }
                 const unsigned long long ballot = __ballot(here);
                 if (here) {
                     const int a = (int)(((float)tap + 0.5f) * p.inv_kw), b = tap - a * p.kw;
                     const int shift = a * p.W + b;
                     const int at = place + __popcll(ballot & ((1ull << lane) - 1ull));
-                    list[2 * at] = (uint32_t)e | (uint32_t)tap << 16 | (uint32_t)(shift & 1) << 24;
-                    list[2 * at + 1] = (uint32_t)((shift >> 1) * sc.pitch + (cb - q * sc.CBC) * (B * 2));
+                    list[2 * at] = SPAN ? (uint32_t)e : (uint32_t)e | (uint32_t)tap << 16 | (uint32_t)(shift & 1) << 24;
+                    list[2 * at + 1] = SPAN ? (uint32_t)(bj * (B / 8)) : (uint32_t)((shift >> 1) * sc.pitch + (cb - q * sc.CBC) * (B * 2));
                 }
                 place += __popcll(ballot);
             }
@@ -185,6 +202,16 @@ void conv_tile_kernel(SpmmArgs p, ConvTileSched sc) {
         }
         if (lane < R) { list[2 * (place + lane)] = CONV_TILE_IDLE; list[2 * (place + lane) + 1] = 0u; }
     }
+    auto fill_octets = [&](int q) __attribute__((always_inline)) {
+        for (int o = tid; o < sc.octets; o += 64 * nwaves) {
+            const int k = o * 8, tap = (int)(((float)k + 0.5f) * p.inv_C), c = k - tap * p.C - q * sc.CC;
+            const int a = (int)(((float)tap + 0.5f) * p.inv_kw), b = tap - a * p.kw;
+            const int shift = a * p.W + b;
+            octets[o] = k < p.K && c >= 0 && c < sc.CC
+                ? (uint32_t)((shift >> 1) * sc.pitch + c * 2) | (uint32_t)tap << 20 | (uint32_t)(shift & 1) << 30 : 31u << 20;
+        }
+    };
+    if constexpr (SPAN) fill_octets(0);
     if (tid < 8) reinterpret_cast<u32x4*>(lds + zero_row)[tid] = u32x4{0u, 0u, 0u, 0u};
     if constexpr (LUT48) lut48_fill(lut48, tid, 64 * nwaves);
 
@@ -212,15 +239,32 @@ void conv_tile_kernel(SpmmArgs p, ConvTileSched sc) {
                 for (int i = 0; i < F::WPR; ++i)
                     ws[rt][i] = __builtin_amdgcn_alignbit(i + 1 < F::WPR ? aw[rt][i + 1] : 0u, aw[rt][i], aw_sh);
         }
-        const int tap = (int)(what >> 16) & 31;
-        const bool odd = (what >> 24) & 1u;
+        // the eight K-rows of the lane's half of 16-deep step ks, at its columns
         const unsigned char* base[NACC];
+        if constexpr (!SPAN) {
+            const int tap = (int)(what >> 16) & 31;
+            const bool odd = (what >> 24) & 1u;
 #pragma unroll
-        for (int c = 0; c < NACC; ++c) {
-            const uint32_t in = (uint32_t)__builtin_amdgcn_sbfe((int)inside[c], tap, 1);
-            const uint32_t at = (odd ? base_odd[c] : base_even[c]) + off;
-            base[c] = lds + ((at & in) | ((uint32_t)zero_row & ~in));
+            for (int c = 0; c < NACC; ++c) {
+                const uint32_t in = (uint32_t)__builtin_amdgcn_sbfe((int)inside[c], tap, 1);
+                const uint32_t at = (odd ? base_odd[c] : base_even[c]) + off;
+                base[c] = lds + ((at & in) | ((uint32_t)zero_row & ~in));
+            }
         }
+        uint32_t oct[SPAN ? KS : 1];
+        if constexpr (SPAN) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) oct[ks] = octets[off + ks * 2 + hh];
+        }
+        auto rows_at = [&](int c, int ks) __attribute__((always_inline)) {
+            if constexpr (SPAN) {
+                const uint32_t in = (uint32_t)((int)(inside[c] << (31u - (oct[ks] >> 20 & 31u))) >> 31);
+                const uint32_t at = ((oct[ks] >> 30) ? base_odd[c] : base_even[c]) + (oct[ks] & 0xFFFFFu);
+                return *reinterpret_cast<const u32x4*>(lds + ((at & in) | ((uint32_t)zero_row & ~in)));
+            } else {
+                return *reinterpret_cast<const u32x4*>(base[c] + ks * 32);
+            }
+        };
         if constexpr (SMF) {
             typedef __attribute__((ext_vector_type(8))) uint32_t u32x8;
             auto sparse_step = [&](auto s2_c) __attribute__((always_inline)) {
@@ -228,8 +272,8 @@ void conv_tile_kernel(SpmmArgs p, ConvTileSched sc) {
                 u32x8 b8[NACC];
 #pragma unroll
                 for (int c = 0; c < NACC; ++c) {
-                    const u32x4 l4 = *reinterpret_cast<const u32x4*>(base[c] + (2 * s2) * 32);
-                    const u32x4 h4 = *reinterpret_cast<const u32x4*>(base[c] + (2 * s2 + 1) * 32);
+                    const u32x4 l4 = rows_at(c, 2 * s2);
+                    const u32x4 h4 = rows_at(c, 2 * s2 + 1);
                     b8[c] = u32x8{l4[0], l4[1], l4[2], l4[3], h4[0], h4[1], h4[2], h4[3]};
                 }
 #pragma unroll
@@ -251,7 +295,7 @@ void conv_tile_kernel(SpmmArgs p, ConvTileSched sc) {
                 constexpr int ks = decltype(ks_c)::value;
                 bf16x8 bfrag[NACC];
 #pragma unroll
-                for (int c = 0; c < NACC; ++c) bfrag[c] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(base[c] + ks * 32));
+                for (int c = 0; c < NACC; ++c) bfrag[c] = __builtin_bit_cast(bf16x8, rows_at(c, ks));
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) {
                     u32x4 a4;
@@ -276,6 +320,7 @@ void conv_tile_kernel(SpmmArgs p, ConvTileSched sc) {
     for (int q = 0; q < sc.chunks; ++q) {
         if (q > 0) {
             __syncthreads();                       // everybody is done with the previous chunk
+            if constexpr (SPAN) fill_octets(q);
             stage(q, wave);
         }
         __syncthreads();
@@ -333,7 +378,7 @@ void conv_tile_kernel(SpmmArgs p, ConvTileSched sc) {
     }
 }
 
-template <int N, int M, int B, int NC2, bool SMF>
+template <int N, int M, int B, int NC2, bool SMF, bool SPAN>
 hipError_t launch_conv_tile_k(const SpmmArgs& a, const ConvTileSched& s, hipStream_t st) {
     const int64_t wgs = (int64_t)((s.tiles + 7) / 8) * 8 * s.row_groups;
     if (wgs > INT32_MAX) return hipErrorInvalidValue;
@@ -343,7 +388,7 @@ hipError_t launch_conv_tile_k(const SpmmArgs& a, const ConvTileSched& s, hipStre
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
         if (!(raised.load() >> dev & 1)) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_tile_kernel<N, M, B, NC2, SMF>),
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_tile_kernel<N, M, B, NC2, SMF, SPAN>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, CONV_TILE_MAX_LDS);
             if (e != hipSuccess) return e;
             raised.fetch_or((uint64_t)1 << dev);
@@ -351,17 +396,22 @@ hipError_t launch_conv_tile_k(const SpmmArgs& a, const ConvTileSched& s, hipStre
     }
     const dim3 grd((unsigned)wgs), blk(64 * s.RG * s.PT);
     if (a.ev_start || a.ev_stop)
-        hipExtLaunchKernelGGL((conv_tile_kernel<N, M, B, NC2, SMF>), grd, blk, (size_t)s.lds_bytes, st, a.ev_start, a.ev_stop, 0, a, s);
+        hipExtLaunchKernelGGL((conv_tile_kernel<N, M, B, NC2, SMF, SPAN>), grd, blk, (size_t)s.lds_bytes, st, a.ev_start, a.ev_stop, 0, a, s);
     else
-        conv_tile_kernel<N, M, B, NC2, SMF><<<grd, blk, (size_t)s.lds_bytes, st>>>(a, s);
+        conv_tile_kernel<N, M, B, NC2, SMF, SPAN><<<grd, blk, (size_t)s.lds_bytes, st>>>(a, s);
     return hipGetLastError();
+}
+
+template <int N, int M, int B, bool SPAN>
+hipError_t launch_conv_tile_b(const SpmmArgs& a, const ConvTileSched& s, hipStream_t st) {
+    constexpr bool SMF = smf_pattern<N, M>();
+    return s.NC2 == 2 ? launch_conv_tile_k<N, M, B, 2, SMF, SPAN>(a, s, st) : launch_conv_tile_k<N, M, B, 1, SMF, SPAN>(a, s, st);
 }
 
 template <int N, int M>
 hipError_t launch_conv_tile(const SpmmArgs& a, int B, const ConvTileSched& s, hipStream_t st) {
-    constexpr bool SMF = smf_pattern<N, M>();
-    if (B == 64) return s.NC2 == 2 ? launch_conv_tile_k<N, M, 64, 2, SMF>(a, s, st) : launch_conv_tile_k<N, M, 64, 1, SMF>(a, s, st);
-    return s.NC2 == 2 ? launch_conv_tile_k<N, M, 32, 2, SMF>(a, s, st) : launch_conv_tile_k<N, M, 32, 1, SMF>(a, s, st);
+    if (s.octets) return B == 64 ? launch_conv_tile_b<N, M, 64, true>(a, s, st) : launch_conv_tile_b<N, M, 32, true>(a, s, st);
+    return B == 64 ? launch_conv_tile_b<N, M, 64, false>(a, s, st) : launch_conv_tile_b<N, M, 32, false>(a, s, st);
 }
 
 }  // namespace crisp

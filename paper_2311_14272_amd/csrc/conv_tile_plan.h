@@ -13,7 +13,7 @@ constexpr int CONV_TILE_MAX_WINDOW = 4096;       // positions staged at once
 
 // The convolution as the schedule sees it.
 struct ConvShape {
-    int Sb, n, m, B, Kb, out_bytes;              // block-rows, pattern, block edge, block columns, bytes of an output
+    int Sb, n, m, B, Kb;                         // block-rows, pattern, block edge, block columns
     int64_t Ncol, plane;                         // output columns, elements of one channel plane
     int C, H, W, kh, kw, stride, pad, Ho, Wo;
 };
@@ -41,6 +41,7 @@ struct ConvTileSched {
     int HP;                  // LDS rows of even positions (as many for the odd ones)
     int pitch;               // bytes of an LDS row
     int list_cap;            // entries of a block-row's list
+    int octets;              // octets of K-rows (rounded up to whole blocks) where a block column holds several taps, else 0
     int lds_bytes;
     DivBy by_Wo, by_Ho, by_unit;   // output width and height, tiles per unit
 };
@@ -91,33 +92,49 @@ inline bool conv_tile_plan(const ConvShape& a, int RG, int PT, int NC2, int imag
     }
     if (window > CONV_TILE_MAX_WINDOW) return false;
     s.HP = (int)(window + 1) / 2;
-    s.CB = (int)((unsigned)a.C / (unsigned)a.B);
-    const int fixed = 128 + RG * 8 * (a.Kb + 2 * s.CB + 4);
-    // as many channel blocks per chunk as fit, evenly
-    int cbc = ((max_lds - fixed) / (2 * s.HP) - 16) / (a.B * 2);
-    if (cbc < 1) return false;
-    if (cbc >= s.CB) {
-        s.CBC = s.CB;
-        s.chunks = 1;
+    if ((unsigned)a.C % (unsigned)a.B != 0) {
+        // block columns that span taps: chunks of whole staging units, and a table of the octets of K-rows
+        s.CB = s.CBC = a.Kb;
+        s.octets = a.Kb * (a.B / 8);
+        const int most = ((max_lds - 144 - s.octets * 4 - RG * 8 * (a.Kb + 4)) / (2 * s.HP) - 16) / 32 * 16 - 16;
+        if (most < 16) return false;
+        s.chunks = a.C <= most ? 1 : (a.C + most - 1) / most;
+        s.CC = s.chunks == 1 ? a.C : (a.C + s.chunks * 16 - 1) / (s.chunks * 16) * 16;
+        s.chunks = (a.C + s.CC - 1) / s.CC;
+        s.pitch = ((s.CC + 7) / 8 | 1) * 16;
+        if ((int64_t)(a.kh * a.W / 2 + 1) * s.pitch >= (1 << 20)) return false;      // a place has 20 bits in the table
     } else {
-        s.chunks = (s.CB + cbc - 1) / cbc;
-        s.CBC = (s.CB + s.chunks - 1) / s.chunks;
-        s.chunks = (s.CB + s.CBC - 1) / s.CBC;
+        s.CB = (int)((unsigned)a.C / (unsigned)a.B);
+        s.octets = 0;
+        const int fixed = 128 + RG * 8 * (a.Kb + 2 * s.CB + 4);
+        // as many channel blocks per chunk as fit, evenly
+        int cbc = ((max_lds - fixed) / (2 * s.HP) - 16) / (a.B * 2);
+        if (cbc < 1) return false;
+        if (cbc >= s.CB) {
+            s.CBC = s.CB;
+            s.chunks = 1;
+        } else {
+            s.chunks = (s.CB + cbc - 1) / cbc;
+            s.CBC = (s.CB + s.chunks - 1) / s.chunks;
+            s.chunks = (s.CB + s.CBC - 1) / s.CBC;
+        }
+        s.CC = s.CBC * a.B;
+        s.pitch = s.CC * 2 + 16;
     }
-    s.CC = s.CBC * a.B;
-    s.pitch = s.CC * 2 + 16;
-    s.list_cap = a.Kb + s.chunks + 2;
-    s.lds_bytes = (2 * s.HP * s.pitch + 128 + RG * (s.list_cap * 8 + s.chunks * 4) + 15) / 16 * 16;
+    // (a block that spans taps is walked in every chunk it has a part in: at most one more entry per tap and chunk)
+    s.list_cap = a.Kb + s.chunks + 2 + (s.octets && s.chunks > 1 ? a.kh * a.kw * s.chunks : 0);
+    s.lds_bytes = (2 * s.HP * s.pitch + 128 + RG * (s.list_cap * 8 + s.chunks * 4) + s.octets * 4 + 15) / 16 * 16;
     return s.lds_bytes <= max_lds;
 }
 
 // What the kernel takes at all.
 inline bool conv_tile_covers(const ConvShape& a) {
-    return a.B >= 32 && a.C % a.B == 0 && a.kh * a.kw <= CONV_TILE_MAX_TAPS && a.Kb <= CONV_TILE_MAX_KB && (a.Ncol & 1) == 0 && a.W >= 4 &&
+    return a.B >= 32 && a.C % 8 == 0 && a.kh * a.kw < CONV_TILE_MAX_TAPS && a.Kb <= CONV_TILE_MAX_KB && (a.Ncol & 1) == 0 && a.W >= 4 &&
            a.pad < a.kh && a.plane < ((int64_t)1 << 26) && a.Ncol < ((int64_t)1 << 30);
 }
 
-// Estimated time of a schedule in clocks of a compute unit (bpr: kept blocks per block-row).  A workgroup's phases follow
+// Estimated time of a schedule in clocks of a compute unit (bpr: kept blocks per block-row; bf16 outputs, so that the choice
+// and with it the order of the sums is the same for both output types).  A workgroup's phases follow
 // one another: window in (9 bytes per clock and compute unit when all stage at once: 5 TB/s), blocks, rows out; two and
 // more workgroups of a compute unit overlap theirs.
 inline double conv_tile_cost(const ConvShape& a, const ConvTileSched& s, int bpr) {
@@ -126,11 +143,12 @@ inline double conv_tile_cost(const ConvShape& a, const ConvTileSched& s, int bpr
     const int per_cu = fit < room ? fit : room;
     const int wgs = s.tiles * s.row_groups;
     const double matrix = (a.n <= 2 ? 256.0 : 512.0) * s.NC2 * (a.B == 64 ? 1.0 : 0.25);
-    const double vector = (a.n == 3 ? 1300.0 : a.n == 4 && a.m == 8 ? 450.0 : a.n == 2 && a.m == 8 ? 430.0 : 200.0) * (a.B == 64 ? 1.0 : 0.3) + 60.0 * s.NC2;
+    const double vector = (a.n == 3 ? 1300.0 : a.n == 4 && a.m == 8 ? 450.0 : a.n == 2 && a.m == 8 ? 430.0 : 200.0) * (a.B == 64 ? 1.0 : 0.3) + 60.0 * s.NC2 +
+                          (s.octets ? (a.B == 64 ? 128.0 : 64.0) * s.NC2 : 0.0);
     const double block = waves / 4.0 * (matrix + 0.5 * vector);
     const double in = 2.0 * s.HP * a.C * 2 / 9.0 + 3000.0 * s.chunks;
-    const double out = (double)(s.RG < a.Sb ? s.RG : a.Sb) * a.B * s.TC * a.out_bytes / 9.0;
-    const double walk = bpr * block * (1.0 + 0.12 * (s.chunks - 1));
+    const double out = (double)(s.RG < a.Sb ? s.RG : a.Sb) * a.B * s.TC * 2 / 9.0;
+    const double walk = bpr * block * (1.0 + 0.12 * (s.chunks - 1)) * (s.octets && s.chunks > 1 ? 1.0 + (double)a.B / s.CC : 1.0);
     const double mem = in + out, rounds = (double)(((unsigned)wgs + 256u * per_cu - 1) / (256u * per_cu));
     const double one = per_cu == 1 ? mem + walk : (mem > walk ? mem * per_cu + walk : walk * per_cu + mem);
     return rounds * (5000.0 + one);
@@ -165,17 +183,28 @@ inline bool conv_tile_choose(const ConvShape& a, int bpr, ConvTileSched* out, do
     return true;
 }
 
-// Whether it is the faster choice against the register kernels, the kernel that stages whole output rows (conv_lds.h) and
-// a materialised X, in microseconds: 10 for a launch and a block list, and per kept block and 64 columns of a compute
-// unit 0.4 where column pairs come from one load, 1.3 where columns are located one by one (32 x 32 blocks a third).
-// Over 300 random convolutions (3x3 and 5x5, stride 1 and 2, 32 to 512 channels, images of 7x7 to 56x56, batch 1 to 256,
-// all patterns, both block sizes, densities 0.2 to 0.8) the rule keeps all but 0.5 % of what the better of both gives
-// each time (geometric mean 1.19 over the whole set, up to 3.6); it is wrong by more than 3 % in four of them (up to
-// 1.21: 144 x 2880 x 8134 3:4).  A strided 1x1 filter leaves out three quarters of what would be staged: 0.4-1.3, not taken.
-inline bool conv_tile_pays(const ConvShape& a, int bpr, double cost) {
-    const bool paired = a.stride == 1;
-    const double blocks = (double)a.Sb * (double)((a.Ncol + 63) / 64) * bpr / 256.0 * (a.B == 64 ? 1.0 : 0.3);
-    return a.kh * a.kw > 1 && cost / 2100.0 + 6.0 < 10.0 + blocks * (paired ? 0.4 : 1.3);
+// What would run instead.
+enum ConvTileRival { RIVAL_FUSED = 0, RIVAL_PATCH = 1, RIVAL_IM2COL = 2 };
+
+// Whether it is the faster choice, in microseconds.  bt: kept blocks x 64 columns per compute unit (a 32 x 32 block counts a
+// third).  Channel counts that are multiples of the block edge: against the register kernels, the kernel that stages whole
+// output rows (conv_lds.h) and a materialised X, 10 for a launch and a block list plus, per bt, 0.4 where column pairs
+// come from one load and 1.3 where columns are located one by one.  Over 300 random convolutions (3x3 and 5x5, stride 1
+// and 2, 32 to 512 channels, images of 7x7 to 56x56, batch 1 to 256, all patterns, both block sizes, densities 0.2 to
+// 0.8) the rule keeps all but 0.5 % of what the better of both gives each time (geometric mean 1.19 over the whole set,
+// up to 3.6) and is wrong by more than 3 % in four of them (up to 1.21: 144 x 2880 x 8134 3:4).
+// Other multiples of eight, 180 more: the register kernels split every K-row into tap and channel (2 per bt, 0.5 per
+// block of the chain); the few-channel kernel takes 17 and more whatever the size; a materialised X is written and read
+// once (5 TB/s).  Geometric mean 1.38 of 1.41 possible; wrong by up to 1.22 (128 x 2232 x 3600 2:8: 20 against 16 us).
+// A strided 1x1 filter leaves out three quarters of what would be staged: 0.4-1.3, not taken.
+inline bool conv_tile_pays(const ConvShape& a, int bpr, double cost, ConvTileRival rival) {
+    if (a.kh * a.kw <= 1) return false;
+    const double us = cost / 2100.0 + 6.0;
+    const double bt = (double)a.Sb * (double)((a.Ncol + 63) / 64) * bpr / 256.0 * (a.B == 64 ? 1.0 : 0.3);
+    if (a.C % a.B == 0) return us < 10.0 + bt * (a.stride == 1 ? 0.4 : 1.3);
+    if (rival == RIVAL_PATCH) return us < 15.0 + bt * 0.3;
+    if (rival == RIVAL_IM2COL) return us < 13.0 + bt * 0.3 + 1.5 * 4e-6 / 5.0 * ((double)a.kh * a.kw * a.C) * (double)a.Ncol;
+    return us * 1.1 < 7.0 + bt * 2.0 + 0.5 * bpr;
 }
 
 }  // namespace crisp

@@ -537,8 +537,11 @@ crisp_status crisp_conv_forward(const crisp_layer_desc* desc, const crisp_conv_d
         if (ldy <= ((int64_t)1 << 23) && !(ep && ep->residual && ep->ldr > ((int64_t)1 << 23)) &&
             !misaligned(x_scratch, 16) && !misaligned(row_ptr, 4) && !misaligned(col_idx, 4) &&
             fused_lowering_covers(g, *conv, Ncol, (int64_t)conv->batch * conv->H * conv->W) &&
-            conv_tile_would_run(g, desc->block_density, *conv, Ncol, y_dtype))
-            path = CRISP_CONV_FUSED;
+            conv_tile_beats_im2col(g, desc->block_density, *conv, Ncol)) {
+            if (path_taken) *path_taken = CRISP_CONV_FUSED;
+            return conv_spmm_impl(desc, conv, row_ptr, col_idx, vals, idx_words, act, Y, ldy, y_dtype, CRISP_SHAPE_CONV_TILE, nullptr,
+                                  stream, nullptr, nullptr, ep);
+        }
     }
     if (path_taken) *path_taken = path;
     if (path == CRISP_CONV_DIRECT)

@@ -48,8 +48,9 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
 
 // Whether launch_spmm would run this convolution with the input patch staged in LDS (host only).
 bool conv_lds_suits(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol);
-// Whether it would run it from a window of input positions in LDS (asked before X is materialised).
-bool conv_tile_would_run(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol, int y_dtype);
+// Whether the kernel that runs it from a window of input positions in LDS (CRISP_SHAPE_CONV_TILE) is expected to be faster
+// than a materialised X.
+bool conv_tile_beats_im2col(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol);
 bool xlds_conv_would_run(const Geometry& g, const crisp_conv_desc& conv, int64_t Ncol);
 
 #define CRISP_BUDGET_MAX_LAYERS 64

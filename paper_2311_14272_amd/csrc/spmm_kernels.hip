@@ -580,24 +580,24 @@ static int blocks_per_row(const Geometry& g, double density_hint) {
     return bpr < 1 ? 1 : bpr;
 }
 
-// Schedule of the convolution kernel with a window of input positions in LDS; false where it does not apply or, with
-// must_pay, is not expected to be the faster one.
-static bool conv_tile_schedule(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol, int out_bytes, bool must_pay,
-                               ConvTileSched* s) {
-    ConvShape c;
-    c.Sb = g.Sb; c.n = g.n; c.m = g.m; c.B = g.B; c.Kb = g.Kb; c.out_bytes = out_bytes;
-    c.Ncol = Ncol; c.plane = (int64_t)conv.batch * conv.H * conv.W;
-    c.C = conv.C; c.H = conv.H; c.W = conv.W; c.kh = conv.kh; c.kw = conv.kw; c.stride = conv.stride; c.pad = conv.pad;
-    c.Ho = (conv.H + 2 * conv.pad - conv.kh) / conv.stride + 1;
-    c.Wo = (conv.W + 2 * conv.pad - conv.kw) / conv.stride + 1;
-    const int bpr = blocks_per_row(g, density_hint);
-    double cost = 0.0;
-    return conv_tile_covers(c) && !(must_pay && c.kh * c.kw == 1) && conv_tile_choose(c, bpr, s, &cost) && (!must_pay || conv_tile_pays(c, bpr, cost));
+// Schedule of the convolution kernel with a window of input positions in LDS and its estimated time; false where it does
+// not apply.
+static bool conv_tile_schedule(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol, ConvShape* c,
+                               ConvTileSched* s, double* cost) {
+    c->Sb = g.Sb; c->n = g.n; c->m = g.m; c->B = g.B; c->Kb = g.Kb;
+    c->Ncol = Ncol; c->plane = (int64_t)conv.batch * conv.H * conv.W;
+    c->C = conv.C; c->H = conv.H; c->W = conv.W; c->kh = conv.kh; c->kw = conv.kw; c->stride = conv.stride; c->pad = conv.pad;
+    c->Ho = (conv.H + 2 * conv.pad - conv.kh) / conv.stride + 1;
+    c->Wo = (conv.W + 2 * conv.pad - conv.kw) / conv.stride + 1;
+    return conv_tile_covers(*c) && conv_tile_choose(*c, blocks_per_row(g, density_hint), s, cost);
 }
 
-bool conv_tile_would_run(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol, int y_dtype) {
+bool conv_tile_beats_im2col(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol) {
+    ConvShape c;
     ConvTileSched s;
-    return conv_tile_schedule(g, density_hint, conv, Ncol, y_dtype == CRISP_Y_BF16 ? 2 : 4, true, &s);
+    double cost = 0.0;
+    return conv.kh * conv.kw > 1 && conv_tile_schedule(g, density_hint, conv, Ncol, &c, &s, &cost) &&
+           conv_tile_pays(c, blocks_per_row(g, density_hint), cost, RIVAL_IM2COL);
 }
 
 hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows, int force_shape, const int32_t* row_ptr,
@@ -650,10 +650,18 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
         }
     }
     if (g.B == 16) { report(CRISP_KERNEL_B16, 0, 0, 0); return launch_b16(a, st); }
+    // channel counts that are no multiple of the block size (first layers): input patch in LDS in its
+    // own layout (forced shape 14)
+    ConvPatchSched ps;
+    const bool patch_ok = conv && (force_shape == 14 || force_shape < 0) && ld_wide <= ((int64_t)1 << 23) &&
+                          conv_patch_plan(a, g.B, conv->kh, g.Kb, &ps);
     // convolution from a window of input positions in LDS (forced shape 19)
     ConvTileSched ts;
-    if (conv && (force_shape == CRISP_SHAPE_CONV_TILE || force_shape < 0) && ld_wide <= ((int64_t)1 << 23) &&
-        conv_tile_schedule(g, density_hint, *conv, Ncol, a.y_bf16 ? 2 : 4, force_shape < 0, &ts)) {
+    ConvShape tshape;
+    double tcost = 0.0;
+    if (conv && (force_shape == CRISP_SHAPE_CONV_TILE || (force_shape < 0 && conv->kh * conv->kw > 1)) && ld_wide <= ((int64_t)1 << 23) &&
+        conv_tile_schedule(g, density_hint, *conv, Ncol, &tshape, &ts, &tcost) &&
+        (force_shape >= 0 || conv_tile_pays(tshape, blocks_per_row(g, density_hint), tcost, patch_ok ? RIVAL_PATCH : RIVAL_FUSED))) {
         report(CRISP_KERNEL_CONV_LDS, ts.NC2, a.conv_mode, g.n <= 2);
         switch (g.n * 16 + g.m) {
             case 1 * 16 + 4: return launch_conv_tile_nm<1, 4>(a, g.B, ts, st);
@@ -686,11 +694,7 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
             default: break;
         }
     }
-    // channel counts that are no multiple of the block size (first layers): input patch in LDS in its
-    // own layout (forced shape 14)
-    ConvPatchSched ps;
-    if (conv && (force_shape == 14 || force_shape < 0) && ld_wide <= ((int64_t)1 << 23) &&
-        conv_patch_plan(a, g.B, conv->kh, g.Kb, &ps)) {
+    if (patch_ok) {
         a.use_smf = 1;
         report(CRISP_KERNEL_CONV_PATCH, 0, a.conv_mode, g.n <= 2);
         switch (g.n * 16 + g.m) {

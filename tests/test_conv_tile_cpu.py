@@ -29,7 +29,26 @@ static void walk(const ConvShape& a, const ConvTileSched& s) {
     const int HoWo = a.Ho * a.Wo;
     std::vector<char> seen((size_t)a.Ncol, 0);
     if (s.lds_bytes < 2 * s.HP * s.pitch + 128 + s.RG * (s.list_cap * 8 + s.chunks * 4) || s.lds_bytes > CONV_TILE_MAX_LDS) fail("LDS", a, s, -1);
-    if (s.pitch != s.CC * 2 + 16 || s.CC != s.CBC * a.B || s.chunks * s.CBC < s.CB || (s.chunks - 1) * s.CBC >= s.CB || s.CB * a.B != a.C) fail("chunks", a, s, -1);
+    if (s.pitch < s.CC * 2 || s.pitch % 32 != 16) fail("pitch", a, s, -1);
+    if (a.C % a.B) {                                          // block columns of several taps: one chunk and a table of octets
+        if (s.octets * 8 != a.Kb * a.B || s.octets * 8 < a.kh * a.kw * a.C || (s.chunks > 1 && s.CC % 16)) fail("octets", a, s, -1);
+        if (s.chunks * s.CC < a.C || (s.chunks - 1) * s.CC >= a.C) fail("chunks", a, s, -1);
+        if ((int64_t)((a.kh - 1) * a.W + a.kw) / 2 * s.pitch + s.CC * 2 >= 1 << 20) fail("place", a, s, -1);
+        if (s.lds_bytes < 2 * s.HP * s.pitch + 128 + s.RG * (s.list_cap * 8 + s.chunks * 4) + s.octets * 4) fail("LDS", a, s, -1);
+        int entries = 2;                                     // what the kernel lists, every block kept
+        for (int q = 0; q < s.chunks; ++q) {
+            int run = 0;
+            for (int bj = 0; bj < a.Kb; ++bj) {
+                bool any = false;
+                for (int k = bj * a.B; k < (bj + 1) * a.B && k < a.kh * a.kw * a.C; k += 8) any = any || k % a.C / s.CC == q;
+                run += any;
+            }
+            entries += run + (run & 1);
+        }
+        if (entries > s.list_cap) fail("list", a, s, -1);
+    } else if (s.octets || s.CC != s.CBC * a.B || s.chunks * s.CBC < s.CB || (s.chunks - 1) * s.CBC >= s.CB || s.CB * a.B != a.C) {
+        fail("chunks", a, s, -1);
+    }
     if (s.list_cap < a.Kb + s.chunks + 2 || s.row_groups * s.RG < a.Sb) fail("rows", a, s, -1);
     for (int tile = 0; tile < s.tiles; ++tile) {
         const int un = tile / s.per_unit;
@@ -64,16 +83,16 @@ static void walk(const ConvShape& a, const ConvTileSched& s) {
 int main() {
     for (int d = 1; d < 5000; ++d) for (int n : {0, 1, d - 1, d, d + 1, 1000003, 2147483646, 2147483647, 2147483647 / d * d, 2147483647 / d * d - 1})
         if (n >= 0 && by(n, div_by(d)) != n / d) { printf("%d / %d\n", n, d); ++bad; }
-    for (int H = 1; H <= 15; H += 2) for (int W = 4; W <= 14; W += H == 7 || H == 13 ? 1 : 3) for (int batch : {1, 2, 7, 20})
+    for (int H = 1; H <= 15; H += 2) for (int W = 4; W <= 14; W += H == 7 || H == 13 ? 1 : 3) for (int batch : {1, 2, 13})
     for (int kh = 1; kh <= 5; kh += 2) for (int kw = 1; kw <= 5; kw += 2) for (int stride = 1; stride <= 3; ++stride) for (int pad = 0; pad < kh; ++pad) {
         if (H + 2 * pad < kh || W + 2 * pad < kw) continue;
         ConvShape a;
-        a.n = 2; a.m = 8; a.out_bytes = 2;
+        a.n = 2; a.m = 8;
         a.H = H; a.W = W; a.kh = kh; a.kw = kw; a.stride = stride; a.pad = pad;
         a.Ho = (H + 2 * pad - kh) / stride + 1; a.Wo = (W + 2 * pad - kw) / stride + 1;
         a.Ncol = (int64_t)batch * a.Ho * a.Wo; a.plane = (int64_t)batch * H * W;
-        for (int C : {32, 192, 1024}) for (int Sb : {1, 3, 9}) {
-            a.B = C == 32 ? 32 : 64; a.C = C; a.Sb = Sb; a.Kb = kh * kw * C / a.B;
+        for (int C : {8, 32, 40, 200, 1024}) for (int Sb : {1, 3, 9}) {
+            a.B = C == 32 ? 32 : 64; a.C = C; a.Sb = Sb; a.Kb = (kh * kw * C + a.B - 1) / a.B;
             if (!conv_tile_covers(a)) continue;
             ConvTileSched s;
             double cost = 0;

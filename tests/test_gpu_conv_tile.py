@@ -63,6 +63,11 @@ def _run(cv, layer, act, S, yd, ep=None, guard=8):
     (40, 32, 13, 13, 2, 3, 3, 1, 1, 32, 0.5),      # 32 x 32 blocks
     (352, 160, 14, 14, 4, 3, 3, 2, 1, 32, 0.4),
     (64, 64, 5, 4, 2, 3, 3, 1, 2, 64, 1.0),        # narrowest image, padding of two
+    (72, 24, 14, 14, 2, 3, 3, 1, 1, 64, 0.5),      # block columns of several taps, K no multiple of 16
+    (64, 8, 12, 12, 2, 5, 5, 1, 2, 64, 1.0),
+    (100, 200, 13, 13, 2, 3, 3, 1, 1, 64, 0.4),
+    (96, 40, 20, 20, 2, 3, 3, 2, 1, 32, 0.6),
+    (300, 272, 28, 28, 2, 3, 3, 2, 1, 64, 0.2),    # ... over several chunks
 ], ids=lambda c: "S%d_C%d_%dx%d_k%ds%d_B%d" % (c[0], c[1], c[2], c[3], c[5], c[7], c[9]))
 def test_window_kernel_against_the_oracle(case):
     for n, m in PATTERNS if case[0] * case[1] <= 20000 else ((2, 8), (4, 8)):
