@@ -366,9 +366,10 @@ CRISP_API crisp_status crisp_conv_spmm_ep(const crisp_layer_desc *desc, const cr
  *          the kernel that was launched (family: CRISP_KERNEL_*; shape: the register kernels' launch
  *          shape 0..3; for the LDS-resident family bit 0 = wide strips, bit 1 = the instantiation with
  *          the larger tile capacity; for the staged convolutions 0 = whole output rows, 1 / 2 = a window of
- *          input positions with 64 / 128 columns per wave; else 0; conv_mode: 0 plain X, 1..4 the fused-lowering modes;
+ *          input positions with 64 / 128 columns per wave; for 16 x 16 blocks 0 = any n:m, 1 = a wave
+ *          per block-row, 2 = four waves split its list; else 0; conv_mode: 0 plain X, 1..4 the fused-lowering modes;
  *          sparse: 1 when the sparse matrix-core instruction is used).  Together with (n, m, B) --
- *          B alone for the generic and 16 x 16 families and for the LDS-resident family with sparse = 0,
+ *          B alone for the generic family, the 16 x 16 family's shape 0 and for the LDS-resident family with sparse = 0,
  *          which are not specialised by pattern -- the code names one compiled kernel.
  * Results agree across shapes within the summation-order tolerance.  Errors as for the plain calls.
  */

@@ -24,6 +24,7 @@
 #include "conv_tile.h"
 #include "spmm_balanced.h"
 #include "spmm_k8.h"
+#include "spmm_b16.h"
 
 namespace crisp {
 
@@ -391,6 +392,8 @@ template <int N, int M>
 hipError_t launch_balanced_nm(const SpmmArgs& a, int B, hipStream_t st);
 template <int N, int M>
 hipError_t launch_k8_nm(const SpmmArgs& a, int B, hipStream_t st);
+template <int N, int M>
+hipError_t launch_b16_nm(const SpmmArgs& a, bool split, hipStream_t st);
 
 #define CRISP_INSTANTIATE_NM(N, M)                                                           \
     template <>                                                                              \
@@ -418,6 +421,10 @@ hipError_t launch_k8_nm(const SpmmArgs& a, int B, hipStream_t st);
     template <>                                                                              \
     hipError_t launch_k8_nm<N, M>(const SpmmArgs& a, int B, hipStream_t st) {                \
         return launch_k8<N, M>(a, B, st);                                                    \
+    }                                                                                        \
+    template <>                                                                              \
+    hipError_t launch_b16_nm<N, M>(const SpmmArgs& a, bool split, hipStream_t st) {          \
+        return launch_b16<N, M>(a, split, st);                                               \
     }
 
 }  // namespace crisp

@@ -260,7 +260,7 @@ static hipError_t launch_one(const SpmmArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// 16 x 16 blocks (the paper's smallest block size).  One wave per (block-row, strip of 64 output
+// 16 x 16 blocks, any n:m (the patterns in use have kernels of their own, spmm_b16.h).  One wave per (block-row, strip of 64 output
 // columns); lane (j = lane % 16, q = lane / 16).  v_mfma_f32_16x16x16_bf16: A operand = row j of the
 // block, columns 4q..4q+3; B operand = one X column, K-rows 4q..4q+3; result = column j, rows
 // 4q..4q+3.  The lane loads 4 consecutive X columns (8 bytes) of each of its 4 K-rows and
@@ -344,7 +344,7 @@ __global__ __launch_bounds__(256) void spmm_b16_kernel(SpmmArgs p) {
     }
 }
 
-static hipError_t launch_b16(const SpmmArgs& a, hipStream_t st) {
+static hipError_t launch_b16_any(const SpmmArgs& a, hipStream_t st) {
     SpmmArgs p = a;
     p.NT = (int)((a.Ncol + 255) / 256);
     const int64_t groups = (int64_t)((p.NT + 7) / 8) * p.Sb * 8;
@@ -377,6 +377,14 @@ template <> hipError_t launch_conv_patch_nm<1, 8>(const SpmmArgs&, const ConvPat
 template <> hipError_t launch_conv_patch_nm<2, 8>(const SpmmArgs&, const ConvPatchSched&, int, hipStream_t);
 template <> hipError_t launch_conv_patch_nm<4, 8>(const SpmmArgs&, const ConvPatchSched&, int, hipStream_t);
 template <> hipError_t launch_conv_patch_nm<8, 8>(const SpmmArgs&, const ConvPatchSched&, int, hipStream_t);
+template <> hipError_t launch_b16_nm<1, 4>(const SpmmArgs&, bool, hipStream_t);
+template <> hipError_t launch_b16_nm<2, 4>(const SpmmArgs&, bool, hipStream_t);
+template <> hipError_t launch_b16_nm<3, 4>(const SpmmArgs&, bool, hipStream_t);
+template <> hipError_t launch_b16_nm<4, 4>(const SpmmArgs&, bool, hipStream_t);
+template <> hipError_t launch_b16_nm<1, 8>(const SpmmArgs&, bool, hipStream_t);
+template <> hipError_t launch_b16_nm<2, 8>(const SpmmArgs&, bool, hipStream_t);
+template <> hipError_t launch_b16_nm<4, 8>(const SpmmArgs&, bool, hipStream_t);
+template <> hipError_t launch_b16_nm<8, 8>(const SpmmArgs&, bool, hipStream_t);
 template <> hipError_t launch_k8_nm<1, 4>(const SpmmArgs&, int, hipStream_t);
 template <> hipError_t launch_k8_nm<2, 4>(const SpmmArgs&, int, hipStream_t);
 template <> hipError_t launch_k8_nm<3, 4>(const SpmmArgs&, int, hipStream_t);
@@ -573,6 +581,15 @@ bool conv_lds_suits(const Geometry& g, double density_hint, const crisp_conv_des
     return (Ncol % 4) == 0 && conv_lds_plan(a, g.B, conv.kh, &cs) && conv_lds_reuses(cs, g.Sb, density_hint, conv.batch, a.Wo);
 }
 
+// 16 x 16 blocks: whether four waves split a block-row's list.  Fifty random products (S 16 to 2016, K 64 to 4480, all
+// patterns): below 2048 tiles of 128 columns from eight blocks per row on it takes 0.39-1.07 of the time of a wave per
+// block-row (256 x 2368 x 232, 57 blocks: 7.4 against 15.0 us), with 3900 to 4500 tiles 0.90-0.95 from 100 blocks on and
+// up to 1.03 below, 1.2-1.7 for short rows on many tiles (784 x 256 x 111096, 12 blocks: 232 against 147 us).
+static bool b16_split(const Geometry& g, int64_t Ncol, int bpr) {
+    const int64_t tiles = (int64_t)g.Sb * ((Ncol + 127) / 128);
+    return (tiles < 2048 && bpr >= 8) || (tiles < 8192 && bpr >= 100);
+}
+
 // Kept blocks per block-row as the descriptor states them (a hint: only speed depends on it).
 static int blocks_per_row(const Geometry& g, double density_hint) {
     const bool hint = density_hint > 0.0 && density_hint <= 1.0;
@@ -649,7 +666,23 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
             default: return hipErrorInvalidValue;
         }
     }
-    if (g.B == 16) { report(CRISP_KERNEL_B16, 0, 0, 0); return launch_b16(a, st); }
+    if (g.B == 16) {
+        const bool split = b16_split(g, Ncol, blocks_per_row(g, density_hint));
+        report(CRISP_KERNEL_B16, split ? 2 : 1, 0, 0);
+        switch (g.n * 16 + g.m) {
+            case 1 * 16 + 4: return launch_b16_nm<1, 4>(a, split, st);
+            case 2 * 16 + 4: return launch_b16_nm<2, 4>(a, split, st);
+            case 3 * 16 + 4: return launch_b16_nm<3, 4>(a, split, st);
+            case 4 * 16 + 4: return launch_b16_nm<4, 4>(a, split, st);
+            case 1 * 16 + 8: return launch_b16_nm<1, 8>(a, split, st);
+            case 2 * 16 + 8: return launch_b16_nm<2, 8>(a, split, st);
+            case 4 * 16 + 8: return launch_b16_nm<4, 8>(a, split, st);
+            case 8 * 16 + 8: return launch_b16_nm<8, 8>(a, split, st);
+            default: break;
+        }
+        report(CRISP_KERNEL_B16, 0, 0, 0);       // any other n:m
+        return launch_b16_any(a, st);
+    }
     // channel counts that are no multiple of the block size (first layers): input patch in LDS in its
     // own layout (forced shape 14)
     ConvPatchSched ps;
