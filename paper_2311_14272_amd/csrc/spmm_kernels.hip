@@ -825,6 +825,11 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
                     : (force_shape >= 0 && force_shape <= 3) ? force_shape
                     : (force_shape >= 7 && force_shape <= 10) ? force_shape - 7
                     : pick_shape(g, Ncol, bpr, a.use_smf && smf_ok);
+    // 32 x 32 blocks: a block of X is 16 registers, so two fit in flight where the rows are long enough for it.  Against one
+    // (time over time): lists split over four waves, 28 to 59 blocks per row 0.78-0.95 (192 x 3904 x 329 4:8: 15.7 against
+    // 20.2 us), 6 to 18 blocks 1.00-1.07; ragged sizes from three blocks per row on 0.79-0.94 (320 x 609 x 139960 4:8: 187
+    // against 237 us), two blocks 1.04; own strips on plain X 1.0-1.06, not taken.
+    a.deep = g.B == 32 && (bpr >= 24 || (bpr >= 3 && ((g.K % 16) != 0 || (Ncol % 4) != 0)));
     // the specialised kernels assume whole 16-row MFMA steps of X (K % 16 == 0) and whole groups
     // of four output columns per lane (Ncol % 4 == 0)
     if (conv || (force_shape != 4 && (g.K % 16) == 0 && (Ncol % 4) == 0 && ld_wide <= ((int64_t)1 << 23))) {

@@ -74,6 +74,7 @@ struct SpmmArgs {
     const void* ep_res;       // S x ep_ldr, same element type as Y
     int64_t ep_ldr;
     int use_smf;              // host side only: sparse-MFMA instantiation wanted (eligible patterns)
+    int deep;                 // host side only: 32 x 32 blocks with two blocks of X in flight per wave (plain X)
     int ragged;               // host side only: K % 16 or Ncol % 4 is not 0 (plain X; CONV == 6 instantiations)
     int two_of_four;          // host side only: 4:8 pack with at most two values per aligned four (caller's assertion)
     // host side only: optional events that receive the kernel's own start and stop time stamps
@@ -1199,6 +1200,10 @@ hipError_t launch_reg_shape(const SpmmArgs& a, int shape, hipStream_t st) {
             case 2: return launch_reg<N, M, B, 1, 4, 1, 1>(a, st);
             default: return launch_reg<N, M, B, 1, 8, 1, 1>(a, st);
         }
+    }
+    if constexpr (B == 32) {
+        if (a.deep && a.ragged) return shape <= 1 ? launch_reg<N, M, B, 1, 1, 2, 6>(a, st) : launch_reg<N, M, B, 1, 4, 2, 6>(a, st);
+        if (a.deep && shape == 2) return launch_reg<N, M, B, 1, 4, 2, 0>(a, st);
     }
     if (a.ragged) return shape <= 1 ? launch_reg<N, M, B, 1, 1, 1, 6>(a, st) : launch_reg<N, M, B, 1, 4, 1, 6>(a, st);
     switch (shape) {
