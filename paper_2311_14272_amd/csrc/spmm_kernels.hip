@@ -857,19 +857,19 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
     // (narrow strips, or the split by four).  Time over that of the generic kernel on 1267 random products (S 4 to 2300,
     // K 16 to 4700, up to 130 thousand columns, all patterns and densities, bf16 and fp32 output): 0.14-1.00 with 64x64
     // blocks or patterns of dense expansion, 0.4 in the middle (512 x 2305 x 50003 2:4, 64x64 blocks: 130 against 276
-    // us); with 32x32 blocks and the sparse instruction 0.21-0.87 below 512 tiles, but up to 1.52 on many tiles (699 x 4401 x
-    // 5100 1:8: 72 against 47 us), where the generic kernel's wide strips fetch a block's slices and its lines of X once
-    // for up to 512 columns.  There rows of up to four blocks run here (0.49-1.05), and rows of up to nine for bf16 output,
-    // an X that the last-level cache holds several times over and patterns other than 1:8 (0.56-1.03); the rest stays.
+    // us).  With 32x32 blocks, the sparse instruction, many tiles and long rows the generic kernel's wide strips were ahead
+    // while one block of X was in flight; with two in flight it is 0.38-1.02 over ninety such products (736 x 472 x 195752
+    // 1:4: 342 against 565 us), most with a layer tail, except for 1:8 without one on up to 3500 tiles (1.09-1.29: 699 x
+    // 4401 x 5100 59 against 48 us), which stays, as do 1:8 and very long rows with fp32 output (0.85-1.29, 0.97).
     const int64_t tiles_r = (int64_t)g.Sb * ((Ncol + 63) / 64);
-    const bool many = tiles_r >= 1024 && bpr > 4 &&
-                      !(a.y_bf16 && (int64_t)g.K * ldx * 2 < ((int64_t)48 << 20) && 8 * g.n / g.m > 1 && bpr < 10);
-    const bool long_b32 = g.B == 32 && g.n <= 2 && (many || (tiles_r >= 512 && bpr >= 14));
+    const bool one_of_8 = 8 * g.n / g.m <= 1;
+    const bool generic_b32 = g.B == 32 && g.n <= 2 && !a.ep_on && ((tiles_r >= 1024 && bpr > 4) || (tiles_r >= 512 && bpr >= 14)) &&
+                             ((one_of_8 && bpr >= 15 && tiles_r < 3500) || (!a.y_bf16 && (one_of_8 || bpr >= 64)));
     // Forced narrow strips and the split by four exist here too (1, 2 and 8, 9); any other forced shape but the
     // generic one does not apply and leaves the choice to the rule.
     const bool forced_r = force_shape == CRISP_SHAPE_REG_NARROW || force_shape == CRISP_SHAPE_REG_SPLIT4 ||
                           force_shape == CRISP_SHAPE_SMF_NARROW || force_shape == CRISP_SHAPE_SMF_SPLIT4;
-    if (!conv && force_shape != CRISP_SHAPE_GENERIC && (forced_r || !long_b32) && ld_wide <= ((int64_t)1 << 23) &&
+    if (!conv && force_shape != CRISP_SHAPE_GENERIC && (forced_r || !generic_b32) && ld_wide <= ((int64_t)1 << 23) &&
         ldx <= ((int64_t)1 << 23)) {
         a.ragged = 1;
         a.use_smf = !(forced_r && force_shape <= CRISP_SHAPE_REG_SPLIT4);
