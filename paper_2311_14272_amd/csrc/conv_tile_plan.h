@@ -129,7 +129,7 @@ inline bool conv_tile_plan(const ConvShape& a, int RG, int PT, int NC2, int imag
 
 // What the kernel takes at all.
 inline bool conv_tile_covers(const ConvShape& a) {
-    return a.B >= 32 && a.C % 8 == 0 && a.kh * a.kw < CONV_TILE_MAX_TAPS && a.Kb <= CONV_TILE_MAX_KB && (a.Ncol & 1) == 0 && a.W >= 4 &&
+    return a.B >= 32 && a.C % 8 == 0 && a.kh * a.kw < CONV_TILE_MAX_TAPS && a.Kb <= CONV_TILE_MAX_KB && a.W >= 4 &&
            a.pad < a.kh && a.plane < ((int64_t)1 << 26) && a.Ncol < ((int64_t)1 << 30);
 }
 
@@ -196,14 +196,17 @@ enum ConvTileRival { RIVAL_FUSED = 0, RIVAL_PATCH = 1, RIVAL_IM2COL = 2 };
 // Other multiples of eight, 180 more: the register kernels split every K-row into tap and channel (2 per bt, 0.5 per
 // block of the chain); the few-channel kernel takes 17 and more whatever the size; a materialised X is written and read
 // once (5 TB/s).  Geometric mean 1.38 of 1.41 possible; wrong by up to 1.22 (128 x 2232 x 3600 2:8: 20 against 16 us).
+// An odd number of columns has only the materialised X beside it: 120 random convolutions of the same ranges 1.61 times the
+// speed (368 x 2376 x 142659 1:4 656 / 203 us), seven of them slower by 3 to 8 %.
 // A strided 1x1 filter leaves out three quarters of what would be staged: 0.4-1.3, not taken.
 inline bool conv_tile_pays(const ConvShape& a, int bpr, double cost, ConvTileRival rival) {
     if (a.kh * a.kw <= 1) return false;
     const double us = cost / 2100.0 + 6.0;
     const double bt = (double)a.Sb * (double)((a.Ncol + 63) / 64) * bpr / 256.0 * (a.B == 64 ? 1.0 : 0.3);
+    if (rival == RIVAL_IM2COL && us < 13.0 + bt * 0.3 + 1.5 * 4e-6 / 5.0 * ((double)a.kh * a.kw * a.C) * (double)a.Ncol) return true;
     if (a.C % a.B == 0) return us < 10.0 + bt * (a.stride == 1 ? 0.4 : 1.3);
     if (rival == RIVAL_PATCH) return us < 15.0 + bt * 0.3;
-    if (rival == RIVAL_IM2COL) return us < 13.0 + bt * 0.3 + 1.5 * 4e-6 / 5.0 * ((double)a.kh * a.kw * a.C) * (double)a.Ncol;
+    if (rival == RIVAL_IM2COL) return false;
     return us * 1.1 < 7.0 + bt * 2.0 + 0.5 * bpr;
 }
 

@@ -351,9 +351,10 @@ static crisp_status spmm_impl(const crisp_layer_desc* desc, const int32_t* row_p
 }
 
 // The geometries the fused lowering covers (row strides of Y and of a residual are checked by the caller).
-static bool fused_lowering_covers(const Geometry& g, const crisp_conv_desc& conv, int64_t Ncol, int64_t plane) {
+// odd_ok: an odd number of columns as well, which only the kernel with a window of input positions takes.
+static bool fused_lowering_covers(const Geometry& g, const crisp_conv_desc& conv, int64_t Ncol, int64_t plane, bool odd_ok = false) {
     const bool pattern_ok = (g.m == 4 && g.n <= 4) || (g.m == 8 && (g.n == 1 || g.n == 2 || g.n == 4 || g.n == 8));
-    if (g.B == 16 || (Ncol & 1) || conv.kw > 16 || conv.kh * conv.kw > 64 || conv.stride > 16 ||
+    if (g.B == 16 || ((Ncol & 1) && !odd_ok) || conv.kw > 16 || conv.kh * conv.kw > 64 || conv.stride > 16 ||
         plane > ((int64_t)1 << 27) || !pattern_ok)
         return false;
     // channel counts that are no multiple of B: rows are located one by one inside one buffer range
@@ -365,7 +366,7 @@ static crisp_status conv_spmm_impl(const crisp_layer_desc* desc, const crisp_con
                                    const int32_t* col_idx, const uint16_t* vals, const uint32_t* idx_words,
                                    const uint16_t* act, void* Y, int64_t ldy, int32_t y_dtype, int force_shape,
                                    int32_t* kernel_code, void* stream, void* ev_start, void* ev_stop,
-                                   const crisp_epilogue* ep = nullptr) {
+                                   const crisp_epilogue* ep = nullptr, bool odd_ok = false) {
     Geometry g;
     crisp_status st = make_geometry(desc, false, &g);
     if (st != CRISP_OK) return st;
@@ -387,7 +388,7 @@ static crisp_status conv_spmm_impl(const crisp_layer_desc* desc, const crisp_con
         return CRISP_EALIGN;
     { crisp_status es = check_epilogue(ep, Ncol); if (es != CRISP_OK) return es; }
     // what the fused kernels cover; everything else goes through crisp_im2col + crisp_spmm
-    if (!fused_lowering_covers(g, *conv, Ncol, plane) || ldy > ((int64_t)1 << 23) ||
+    if (!fused_lowering_covers(g, *conv, Ncol, plane, odd_ok) || ldy > ((int64_t)1 << 23) ||
         (ep && ep->residual && ep->ldr > ((int64_t)1 << 23)))
         return CRISP_EUNSUPPORTED;
     // shapes of the fused lowering that may be forced (anything else: the automatic choice)
@@ -536,11 +537,11 @@ crisp_status crisp_conv_forward(const crisp_layer_desc* desc, const crisp_conv_d
         }
         if (ldy <= ((int64_t)1 << 23) && !(ep && ep->residual && ep->ldr > ((int64_t)1 << 23)) &&
             !misaligned(x_scratch, 16) && !misaligned(row_ptr, 4) && !misaligned(col_idx, 4) &&
-            fused_lowering_covers(g, *conv, Ncol, (int64_t)conv->batch * conv->H * conv->W) &&
+            fused_lowering_covers(g, *conv, Ncol, (int64_t)conv->batch * conv->H * conv->W, true) &&
             conv_tile_beats_im2col(g, desc->block_density, *conv, Ncol)) {
             if (path_taken) *path_taken = CRISP_CONV_FUSED;
             return conv_spmm_impl(desc, conv, row_ptr, col_idx, vals, idx_words, act, Y, ldy, y_dtype, CRISP_SHAPE_CONV_TILE, nullptr,
-                                  stream, nullptr, nullptr, ep);
+                                  stream, nullptr, nullptr, ep, true);
         }
     }
     if (path_taken) *path_taken = path;

@@ -56,7 +56,7 @@ static void walk(const ConvShape& a, const ConvTileSched& s) {
         const int first = un * s.unit + (tile - un * s.per_unit) * s.TC;
         const int end = min(min(first + s.TC, (un + 1) * s.unit), (int)a.Ncol);
         if (first >= end) continue;                          // an empty tile stages and stores nothing
-        if ((first & 1) || (end & 1) || end - first > 64 * s.NC2 * s.PT) { fail("columns", a, s, tile); continue; }
+        if ((first & 1) || ((end & 1) && end != a.Ncol) || end - first > 64 * s.NC2 * s.PT) { fail("columns", a, s, tile); continue; }
         const int row0 = by(first, div_by(a.Wo)), row1 = by(end - 1, div_by(a.Wo));
         if (row0 != first / a.Wo || row1 != (end - 1) / a.Wo) fail("division", a, s, tile);
         int lo = 0, npos = 0;

@@ -123,3 +123,33 @@ def test_planned_lowering_gives_way_to_the_window_kernel():
         torch.cuda.synchronize()
         check_product(Y[:, :cv.Ncol].cpu().numpy().astype(np.float64), Yref, Aref, crisp.Y_F32, "batch %d" % b)
         del Y
+
+
+@pytest.mark.parametrize("case,n,m", [
+    ((96, 128, 13, 13, 45, 3, 3, 1, 1, 64, 0.5), 1, 4),
+    ((64, 72, 33, 33, 13, 3, 3, 1, 1, 64, 0.6), 4, 8),
+    ((40, 64, 7, 7, 301, 5, 5, 1, 2, 32, 0.5), 2, 8),
+], ids=str)
+def test_odd_number_of_columns(case, n, m):
+    """Planned through a materialised X, run from the window: the last lane stores one column, with and without a tail."""
+    cv, layer, act, Yref, Aref, _ = _layer(case, n, m)
+    S, N = case[0], cv.Ncol
+    assert N % 2 == 1 and crisp.conv_plan(layer.desc, cv)[0] == "im2col"
+    ld, dact = (N + 7) // 8 * 8, dev(act)
+    X = torch.empty(crisp.conv_plan(layer.desc, cv)[1] // 2, dtype=torch.int16, device="cuda")
+
+    def run(yd, ep=None):
+        Y = torch.full((S + 1, ld), float("nan"), dtype=torch.float32 if yd == crisp.Y_F32 else torch.bfloat16, device="cuda")
+        assert crisp.conv_forward(layer, cv, dact, Y, ld, yd, X, ep) == "fused"
+        torch.cuda.synchronize()
+        Yh = Y.float().cpu().numpy().astype(np.float64)
+        assert np.isnan(Yh[:S, N:]).all() and np.isnan(Yh[S]).all(), "guard band written"
+        return Yh[:S, :N]
+
+    f32 = run(crisp.Y_F32)
+    check_product(f32, Yref, Aref, crisp.Y_F32, str(case))
+    check_bf16_is_rounded_f32(run(crisp.Y_BF16), f32, str(case))
+    g = torch.Generator(device="cuda").manual_seed(5)
+    scale, bias, res = torch.rand(S, generator=g, device="cuda"), torch.randn(S, generator=g, device="cuda"), torch.randn((S, ld), generator=g, device="cuda")
+    want = torch.relu(torch.from_numpy(f32).cuda().float() * scale[:, None] + bias[:, None] + res[:, :N])
+    assert (torch.from_numpy(run(crisp.Y_F32, crisp.epilogue(scale, bias, res, ld, True))).cuda().float() == want).all()
