@@ -424,7 +424,7 @@ CRISP_API crisp_status crisp_conv_spmm_forced(const crisp_layer_desc *desc, cons
  * an input row; everything the fused entry point does not cover is materialised.
  * crisp_conv_plan (host only, pure) reports the way and the scratch bytes it needs (0 unless IM2COL).
  * crisp_conv_forward enqueues it, except that an IM2COL plan is run as FUSED where a fused kernel is known to be the
- * faster one (the scratch is asked for all the same; also an odd number of columns, which crisp_conv_spmm_ep by itself
+ * faster one (small strided convolutions among them; the scratch is asked for all the same; also an odd number of columns, which crisp_conv_spmm_ep by itself
  * does not take); x_scratch may be NULL when no scratch is needed; with Y or residual
  * row strides above 2^23 a FUSED plan is run as IM2COL (then scratch of K x round_up(Ncol, 8) is needed
  * after all); *path_taken (optional, host) receives the way taken.

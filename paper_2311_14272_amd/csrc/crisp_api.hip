@@ -535,13 +535,16 @@ crisp_status crisp_conv_forward(const crisp_layer_desc* desc, const crisp_conv_d
             if (path_taken) *path_taken = path;
             return CRISP_EBUFSIZE;
         }
+        const int64_t plane = (int64_t)conv->batch * conv->H * conv->W;
         if (ldy <= ((int64_t)1 << 23) && !(ep && ep->residual && ep->ldr > ((int64_t)1 << 23)) &&
-            !misaligned(x_scratch, 16) && !misaligned(row_ptr, 4) && !misaligned(col_idx, 4) &&
-            fused_lowering_covers(g, *conv, Ncol, (int64_t)conv->batch * conv->H * conv->W, true) &&
-            conv_tile_beats_im2col(g, desc->block_density, *conv, Ncol)) {
-            if (path_taken) *path_taken = CRISP_CONV_FUSED;
-            return conv_spmm_impl(desc, conv, row_ptr, col_idx, vals, idx_words, act, Y, ldy, y_dtype, CRISP_SHAPE_CONV_TILE, nullptr,
-                                  stream, nullptr, nullptr, ep, true);
+            !misaligned(x_scratch, 16) && !misaligned(row_ptr, 4) && !misaligned(col_idx, 4)) {
+            const bool tile = fused_lowering_covers(g, *conv, Ncol, plane, true) && conv_tile_beats_im2col(g, desc->block_density, *conv, Ncol);
+            if (tile || (desc->select_mode == CRISP_ROW_UNIFORM && fused_lowering_covers(g, *conv, Ncol, plane) &&
+                         conv_reg_beats_im2col(g, desc->block_density, *conv, Ncol))) {
+                if (path_taken) *path_taken = CRISP_CONV_FUSED;
+                return conv_spmm_impl(desc, conv, row_ptr, col_idx, vals, idx_words, act, Y, ldy, y_dtype,
+                                      tile ? CRISP_SHAPE_CONV_TILE : -1, nullptr, stream, nullptr, nullptr, ep, tile);
+            }
         }
     }
     if (path_taken) *path_taken = path;

@@ -51,6 +51,8 @@ bool conv_lds_suits(const Geometry& g, double density_hint, const crisp_conv_des
 // Whether the kernel that runs it from a window of input positions in LDS (CRISP_SHAPE_CONV_TILE) is expected to be faster
 // than a materialised X.
 bool conv_tile_beats_im2col(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol);
+// Whether the fused register kernels are, for a convolution that they cover (rows of equal block counts).
+bool conv_reg_beats_im2col(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol);
 bool xlds_conv_would_run(const Geometry& g, const crisp_conv_desc& conv, int64_t Ncol);
 
 #define CRISP_BUDGET_MAX_LAYERS 64

@@ -617,6 +617,31 @@ bool conv_tile_beats_im2col(const Geometry& g, double density_hint, const crisp_
            conv_tile_pays(c, blocks_per_row(g, density_hint), cost, RIVAL_IM2COL);
 }
 
+// Microseconds, fitted to 380 random convolutions that are planned through a materialised X (strided 1x1, 3x3 and 5x5, images
+// of 7x7 to 56x56, batch 1 to 256, 32 to 1024 channels, of them 110 no multiple of the block edge; all patterns, both block
+// sizes, densities 0.2 to 0.8); bt: kept blocks x 64 columns per compute unit, bq: blocks of a row (a 32 x 32 block counts a
+// third and a half).  Materialising costs a second launch and the write and read of X; the register kernels locate every
+// column again for each kept block (an 8-byte piece per pair in a strided 1x1 filter of even widths) and wait for 2-byte loads
+// down the list, so filters of several taps and channels that are no multiple of the block edge come here with up to 8 blocks
+// a row: longer lists gain 7 % on average, and lose as much in the odd case.  160 x 704 x 1176 2:4 10.6 / 5.9 us, 1792 x 256 x 1400 4:8 13.7 / 9.5,
+// 320 x 576 x 3332 3:4 14.9 / 9.6; against it 592 x 896 x 4624 3:4 38.4 / 70.9, 144 x 8352 x 352 1:4 29.8 / 47.8.
+bool conv_reg_beats_im2col(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol) {
+    SpmmArgs a{};
+    fill_conv_args(a, g, conv);
+    const int bpr = blocks_per_row(g, density_hint);
+    const bool one_tap = conv.kh * conv.kw == 1, spans = a.conv_mode == 3;
+    if ((spans || !one_tap) && bpr > 8) return false;
+    const double bt = (double)g.Sb * (double)((Ncol + 63) / 64) * bpr / 256.0 * (g.B == 64 ? 1.0 : 0.3);
+    const double bq = bpr * (g.B == 64 ? 1.0 : 0.5);
+    const double x_us = 4e-6 / 5.0 * (double)g.K * (double)Ncol;                  // X written and read at 5 TB/s
+    const double fused = spans                ? 6.5 + 0.75 * bt + 0.75 * bq
+                         : a.conv_mode == 4   ? 6.0 + 0.7 * bt
+                         : one_tap            ? 5.7 + 1.25 * bt + 0.08 * bq
+                                              : 5.0 + 0.45 * bt + 0.45 * bq;
+    const double apart = one_tap ? 9.5 + 0.5 * bt + 0.06 * bq + 2.0 * x_us : 9.4 + 0.25 * bt + 0.25 * bq + 1.05 * x_us;
+    return fused * 1.1 < apart;
+}
+
 hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows, int force_shape, const int32_t* row_ptr,
                        const int32_t* col_idx, const uint16_t* vals, const uint32_t* idxw, const uint16_t* X,
                        const crisp_conv_desc* conv, int64_t Ncol, int64_t ldx, void* Y, int64_t ldy, int y_dtype,

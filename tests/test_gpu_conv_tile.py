@@ -108,8 +108,8 @@ def test_planned_lowering_gives_way_to_the_window_kernel():
     """A strided 3x3 layer that is planned through a materialised X: run fused where there are columns enough, with the plan
     and its scratch as they were; through X for few columns and for output rows beyond the fused kernels' stride."""
     S, n, m = 256, 4, 8
-    for b, ldy_extra, expect in ((192, 0, "fused"), (2, 0, "im2col"), (192, (1 << 23) + 8, "im2col")):
-        case = (S, 128, 14, 14, b, 3, 3, 2, 1, 64, 0.45)
+    for b, d, ldy_extra, expect in ((192, 0.45, 0, "fused"), (2, 0.8, 0, "im2col"), (192, 0.45, (1 << 23) + 8, "im2col")):
+        case = (S, 128, 14, 14, b, 3, 3, 2, 1, 64, d)
         cv, layer, act, Yref, Aref, _ = _layer(case, n, m)
         planned, nbytes = crisp.conv_plan(layer.desc, cv)
         assert planned == "im2col" and nbytes == cv.K * ((cv.Ncol + 7) // 8 * 8) * 2
@@ -153,3 +153,34 @@ def test_odd_number_of_columns(case, n, m):
     scale, bias, res = torch.rand(S, generator=g, device="cuda"), torch.randn(S, generator=g, device="cuda"), torch.randn((S, ld), generator=g, device="cuda")
     want = torch.relu(torch.from_numpy(f32).cuda().float() * scale[:, None] + bias[:, None] + res[:, :N])
     assert (torch.from_numpy(run(crisp.Y_F32, crisp.epilogue(scale, bias, res, ld, True))).cuda().float() == want).all()
+
+
+@pytest.mark.parametrize("case,n,m,expect", [
+    ((320, 704, 13, 13, 24, 1, 1, 2, 0, 64, 0.3), 2, 4, "fused"),      # pairs located one by one
+    ((1090, 512, 28, 28, 3, 1, 1, 2, 0, 64, 0.5), 4, 8, "fused"),      # pairs from one 8-byte piece, a remainder of rows
+    ((320, 64, 27, 27, 2, 3, 3, 2, 1, 64, 0.5), 3, 4, "fused"),        # several taps, a short list
+    ((96, 36, 14, 14, 4, 1, 1, 2, 0, 32, 0.5), 1, 8, "fused"),         # channels that are no multiple of the block edge
+    ((320, 64, 27, 27, 2, 3, 3, 2, 1, 32, 0.7), 3, 4, "im2col"),       # several taps, a long list
+    ((592, 896, 33, 33, 16, 1, 1, 2, 0, 32, 0.63), 3, 4, "im2col"),    # much to locate
+], ids=str)
+def test_planned_lowering_gives_way_to_the_register_kernels(case, n, m, expect):
+    """Small strided convolutions planned through a materialised X: one launch where the register kernels take less, with the
+    same results as X and the product give, epilogue included, and the same refusals."""
+    cv, layer, act, Yref, Aref, _ = _layer(case, n, m)
+    S, N = case[0], cv.Ncol
+    planned, nbytes = crisp.conv_plan(layer.desc, cv)
+    assert planned == "im2col" and nbytes == cv.K * ((N + 7) // 8 * 8) * 2
+    ld, dact = (N + 7) // 8 * 8, dev(act)
+    X = torch.empty(nbytes // 2, dtype=torch.int16, device="cuda")
+    Y = torch.full((S + 1, ld), float("nan"), dtype=torch.float32, device="cuda")
+    with pytest.raises(ValueError):
+        crisp.conv_forward(layer, cv, dact, Y, ld, crisp.Y_F32, None)
+    assert crisp.conv_forward(layer, cv, dact, Y, ld, crisp.Y_F32, X) == expect
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(Y[:S, N:]).all()) and bool(torch.isnan(Y[S]).all())
+    plain = Y[:S, :N].clone()
+    check_product(plain.cpu().numpy().astype(np.float64), Yref, Aref, crisp.Y_F32, str(case))
+    g = torch.Generator(device="cuda").manual_seed(5)
+    scale, bias, res = torch.rand(S, generator=g, device="cuda"), torch.randn(S, generator=g, device="cuda"), torch.randn((S, ld), generator=g, device="cuda")
+    assert crisp.conv_forward(layer, cv, dact, Y, ld, crisp.Y_F32, X, crisp.epilogue(scale, bias, res, ld, True)) == expect
+    assert (Y[:S, :N] == torch.relu(plain * scale[:, None] + bias[:, None] + res[:, :N])).all()
