@@ -193,9 +193,11 @@ enum ConvTileRival { RIVAL_FUSED = 0, RIVAL_PATCH = 1, RIVAL_IM2COL = 2 };
 // and 2, 32 to 512 channels, images of 7x7 to 56x56, batch 1 to 256, all patterns, both block sizes, densities 0.2 to
 // 0.8) the rule keeps all but 0.5 % of what the better of both gives each time (geometric mean 1.19 over the whole set,
 // up to 3.6) and is wrong by more than 3 % in four of them (up to 1.21: 144 x 2880 x 8134 3:4).
-// Other multiples of eight, 180 more: the register kernels split every K-row into tap and channel (2 per bt, 0.5 per
-// block of the chain); the few-channel kernel takes 17 and more whatever the size; a materialised X is written and read
-// once (5 TB/s).  Geometric mean 1.38 of 1.41 possible; wrong by up to 1.22 (128 x 2232 x 3600 2:8: 20 against 16 us).
+// Other multiples of eight: the register kernels split every K-row into tap and channel (7, and 0.9 per bt and 0.7 per block
+// of the chain, 0.32 where it is 32 x 32: 193 random convolutions); the few-channel kernel takes 15 and more whatever the
+// size; a materialised X is written and read once (5 TB/s).  Over 250 random convolutions 1.38 times the speed, geometric
+// mean (1.46 with the better of both each time); nine are slower by more than 5 % (two of them by 1.15 and 1.42:
+// 256 x 9200 x 3136 2:4 41 / 58 us, where X stays in the caches).
 // An odd number of columns has only the materialised X beside it: 120 random convolutions of the same ranges 1.61 times the
 // speed (368 x 2376 x 142659 1:4 656 / 203 us), seven of them slower by 3 to 8 %.
 // A strided 1x1 filter leaves out three quarters of what would be staged: 0.4-1.3, not taken.
@@ -207,7 +209,7 @@ inline bool conv_tile_pays(const ConvShape& a, int bpr, double cost, ConvTileRiv
     if (a.C % a.B == 0) return us < 10.0 + bt * (a.stride == 1 ? 0.4 : 1.3);
     if (rival == RIVAL_PATCH) return us < 15.0 + bt * 0.3;
     if (rival == RIVAL_IM2COL) return false;
-    return us * 1.1 < 7.0 + bt * 2.0 + 0.5 * bpr;
+    return us * 1.03 < 7.0 + bt * 0.9 + bpr * (a.B == 64 ? 0.7 : 0.32);
 }
 
 }  // namespace crisp
