@@ -195,9 +195,9 @@ enum ConvTileRival { RIVAL_FUSED = 0, RIVAL_PATCH = 1, RIVAL_IM2COL = 2 };
 // up to 3.6) and is wrong by more than 3 % in four of them (up to 1.21: 144 x 2880 x 8134 3:4).
 // Other multiples of eight: the register kernels split every K-row into tap and channel (7, and 0.9 per bt and 0.7 per block
 // of the chain, 0.32 where it is 32 x 32: 193 random convolutions); the few-channel kernel takes 15 and more whatever the
-// size; a materialised X is written and read once (5 TB/s).  Over 250 random convolutions 1.38 times the speed, geometric
-// mean (1.46 with the better of both each time); nine are slower by more than 5 % (two of them by 1.15 and 1.42:
-// 256 x 9200 x 3136 2:4 41 / 58 us, where X stays in the caches).
+// size; a materialised X is written and read once (5 TB/s).  250 random convolutions run at 1.36 times the speed, geometric
+// mean (160 of them with 24 and more channels mostly: 1.41, 1.46 with the better of both each time); seven are slower by more
+// than 5 % (the worst by 1.15, and 1.42 for 256 x 9200 x 3136 2:4, 41 / 58 us, where X stays in the caches).
 // An odd number of columns has only the materialised X beside it: 120 random convolutions of the same ranges 1.61 times the
 // speed (368 x 2376 x 142659 1:4 656 / 203 us), seven of them slower by 3 to 8 %.
 // A strided 1x1 filter leaves out three quarters of what would be staged: 0.4-1.3, not taken.

@@ -623,8 +623,9 @@ bool conv_tile_beats_im2col(const Geometry& g, double density_hint, const crisp_
 // third and a half).  Materialising costs a second launch and the write and read of X; the register kernels locate every
 // column again for each kept block (an 8-byte piece per pair in a strided 1x1 filter of even widths) and wait for 2-byte loads
 // down the list, so filters of several taps and channels that are no multiple of the block edge come here with up to 8 blocks
-// a row: longer lists gain 7 % on average, and lose as much in the odd case.  160 x 704 x 1176 2:4 10.6 / 5.9 us, 1792 x 256 x 1400 4:8 13.7 / 9.5,
-// 320 x 576 x 3332 3:4 14.9 / 9.6; against it 592 x 896 x 4624 3:4 38.4 / 70.9, 144 x 8352 x 352 1:4 29.8 / 47.8.
+// a row: longer lists gain 7 % on average, and lose as much now and then.  160 x 704 x 1176 2:4 10.6 / 5.9 us,
+// 1792 x 256 x 1400 4:8 13.7 / 9.5, 320 x 576 x 3332 3:4 14.9 / 9.6; against it 592 x 896 x 4624 3:4 38.4 / 70.9,
+// 144 x 8352 x 352 1:4 29.8 / 47.8.  Geometric mean 1.24 over the 380, three slower by 8 to 17 %.
 bool conv_reg_beats_im2col(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol) {
     SpmmArgs a{};
     fill_conv_args(a, g, conv);
