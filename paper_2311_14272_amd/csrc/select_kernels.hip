@@ -21,13 +21,11 @@ namespace crisp {
 // hundred workgroups each, far too few to fill 256 compute units one layer at a time, and a launch has a ramp and a last
 // wave of its own (the 53 layers of ResNet-50: two launches in place of eight, one pair per pattern width and alignment,
 // 82 -> 47 us on the GPU).  Workgroup ids are mapped to (layer, block) through the prefix sums in `first`.
-template <class BATCH>
-__device__ __forceinline__ int layer_of(const BATCH& bt, int id) {
-    constexpr int CAP = sizeof(bt.first) / 4 - 1;
+template <int THREADS, class LAYER, int CAP>
+__device__ __forceinline__ int layer_of(const SelBatch<LAYER, CAP>& bt, int id) {
     if constexpr (CAP == 1) return 0;
-    static_assert(CAP <= 64, "one lane per layer");
     const int lane = threadIdx.x & 63;
-    return __popcll(__ballot(lane > 0 && lane < bt.n && id >= bt.first[lane]));
+    return layer_by_ballots<THREADS, CAP>(bt.n, bt.first, id, [&](auto p) __attribute__((always_inline)) { return __ballot(p(lane)); });
 }
 
 // Saliency, N:M choice and (PACK) packed form of one lane's columns; returns the keep bits.
@@ -51,8 +49,9 @@ __device__ __forceinline__ uint32_t score_lane(const ScoreLayer& sa, const SelSt
 }
 
 template <int B, int KIND, bool PACK, int CAP>
-__global__ __launch_bounds__(B * (B / 16)) void score_select_kernel(SelBatch<ScoreLayer, CAP> bt) {
-    const int li = __builtin_amdgcn_readfirstlane(layer_of(bt, (int)blockIdx.x));
+__global__ __launch_bounds__(score_threads(B)) void score_select_kernel(SelBatch<ScoreLayer, CAP> bt) {
+    constexpr int NTHR = score_threads(B);
+    const int li = __builtin_amdgcn_readfirstlane(layer_of<NTHR>(bt, (int)blockIdx.x));
     const ScoreLayer& sa = bt.L[li];
     const int local = (int)blockIdx.x - bt.first[li];
     const int S = sa.S, K = sa.K;
@@ -62,7 +61,6 @@ __global__ __launch_bounds__(B * (B / 16)) void score_select_kernel(SelBatch<Sco
     constexpr int Q = B / LANE_COLS;  // lanes per block row (1, 2 or 4)
     constexpr int LDT = B + 4;        // padded LDS row stride in floats (keeps 16-byte alignment)
     constexpr int WMAX = (B * 3 + 31) / 32;   // upper bound of position words per block row
-    constexpr int NTHR = B * (B / 16);
     __shared__ __attribute__((aligned(16))) float tkept[B * LDT];
     __shared__ double rowsum[B];
     __shared__ uint32_t pos_lds[PACK ? B * WMAX : 1];
@@ -227,9 +225,9 @@ template <int KIND, bool PACK, int CAP>
 static void launch_score_batch(int B, const SelBatch<ScoreLayer, CAP>& bt, hipStream_t st) {
     const unsigned grid = (unsigned)bt.first[bt.n];
     if (grid == 0) return;
-    if (B == 64) score_select_kernel<64, KIND, PACK, CAP><<<grid, 256, 0, st>>>(bt);
-    else if (B == 32) score_select_kernel<32, KIND, PACK, CAP><<<grid, 64, 0, st>>>(bt);
-    else score_select_kernel<16, KIND, PACK, CAP><<<grid, 16, 0, st>>>(bt);
+    if (B == 64) score_select_kernel<64, KIND, PACK, CAP><<<grid, score_threads(64), 0, st>>>(bt);
+    else if (B == 32) score_select_kernel<32, KIND, PACK, CAP><<<grid, score_threads(32), 0, st>>>(bt);
+    else score_select_kernel<16, KIND, PACK, CAP><<<grid, score_threads(16), 0, st>>>(bt);
 }
 
 template <bool PACK, int CAP>
@@ -259,12 +257,13 @@ hipError_t launch_select(const Geometry& g, int sal_kind, int select_mode, const
 // less than a launch), takes the t-th kept column in ascending order and copies that block's
 // packed form from the staging area to its final place.  Results are identical to
 // crisp_select_mask followed by crisp_pack.
+constexpr int GATHER_THREADS = 256;
 template <int CAP>
-__global__ __launch_bounds__(256) void topk_gather_kernel(SelBatch<GatherLayer, CAP> bt, int B) {
+__global__ __launch_bounds__(GATHER_THREADS) void topk_gather_kernel(SelBatch<GatherLayer, CAP> bt, int B) {
     __shared__ double sc[512];
     __shared__ uint8_t kept[512];
     __shared__ int sel;
-    const int li = __builtin_amdgcn_readfirstlane(layer_of(bt, (int)blockIdx.x));
+    const int li = __builtin_amdgcn_readfirstlane(layer_of<GATHER_THREADS>(bt, (int)blockIdx.x));
     const GatherLayer& L = bt.L[li];
     const int local = (int)blockIdx.x - bt.first[li];
     const int Kb = (int)(L.Kb_k_nm & 0xFFFu), k_row = (int)(L.Kb_k_nm >> 12 & 0xFFFu), Sb = L.Sb;
@@ -272,16 +271,16 @@ __global__ __launch_bounds__(256) void topk_gather_kernel(SelBatch<GatherLayer, 
     const SelStage stg = sel_stage(B, n, m, (size_t)Sb * Kb);
     const int bi = local / k_row, t = local - bi * k_row, tid = threadIdx.x;
     const int vbytes = B * stg.slots * 2, ibytes = B * stg.wpr * 4;
-    for (int j = tid; j < Kb; j += 256) sc[j] = L.score[(size_t)bi * Kb + j];
+    for (int j = tid; j < Kb; j += GATHER_THREADS) sc[j] = L.score[(size_t)bi * Kb + j];
     __syncthreads();
-    for (int j = tid; j < Kb; j += 256) {
+    for (int j = tid; j < Kb; j += GATHER_THREADS) {
         const double mine = sc[j];
         int before = 0;
         for (int o = 0; o < Kb; ++o) before += (sc[o] > mine) || (sc[o] == mine && o < j);
         kept[j] = before < k_row;
     }
     __syncthreads();
-    for (int j = tid; j < Kb; j += 256) {
+    for (int j = tid; j < Kb; j += GATHER_THREADS) {
         if (kept[j]) {
             int pos = 0;
             for (int o = 0; o < j; ++o) pos += kept[o];
@@ -293,10 +292,10 @@ __global__ __launch_bounds__(256) void topk_gather_kernel(SelBatch<GatherLayer, 
     const size_t src = (size_t)bi * Kb + bj, dst = (size_t)bi * k_row + t;
     const u32x4* sv = reinterpret_cast<const u32x4*>(L.stage + stg.vals_off + src * vbytes);
     u32x4* dv = reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(L.vals) + dst * vbytes);
-    for (int e = tid; e < vbytes / 16; e += 256) dv[e] = sv[e];
+    for (int e = tid; e < vbytes / 16; e += GATHER_THREADS) dv[e] = sv[e];
     const u32x4* si = reinterpret_cast<const u32x4*>(L.stage + stg.idxw_off + src * ibytes);
     u32x4* di = reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(L.idxw) + dst * ibytes);
-    for (int e = tid; e < ibytes / 16; e += 256) di[e] = si[e];
+    for (int e = tid; e < ibytes / 16; e += GATHER_THREADS) di[e] = si[e];
     if (tid == 0) {
         L.col_idx[dst] = bj;
         if (t == 0) {
@@ -332,7 +331,7 @@ static hipError_t launch_select_pack(int n, const Geometry* g, int sal_kind, con
         gb.first[i + 1] = gb.first[i] + g[i].nk;
     }
     launch_score_kind<true>(sal_kind, g[0].B, sb, st);
-    if (gb.first[n] > 0) topk_gather_kernel<CAP><<<(unsigned)gb.first[n], 256, 0, st>>>(gb, g[0].B);
+    if (gb.first[n] > 0) topk_gather_kernel<CAP><<<(unsigned)gb.first[n], GATHER_THREADS, 0, st>>>(gb, g[0].B);
     return hipGetLastError();
 }
 

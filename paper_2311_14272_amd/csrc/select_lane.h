@@ -3,6 +3,7 @@
 // (Alg. 1 lines 2 and 4-5; storage format of Sec. 3.1 / 3.5).
 #pragma once
 #include "crisp_internal.h"
+#include "select_layer.h"
 
 namespace crisp {
 
