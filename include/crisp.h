@@ -393,7 +393,9 @@ enum {
     CRISP_SHAPE_LDS_SMF = 16,    /* block-row resident in LDS as sparse matrix-core operands      */
     CRISP_SHAPE_LDS_SMF_30 = 17, /* ... always the instantiation that holds 30 blocks             */
     CRISP_SHAPE_XLDS = 18,       /* K <= 512: a strip of X resident in LDS for all block-rows     */
-    CRISP_SHAPE_CONV_TILE = 19   /* fused lowering with a window of input positions in LDS        */
+    CRISP_SHAPE_CONV_TILE = 19,  /* fused lowering with a window of input positions in LDS        */
+    CRISP_SHAPE_CONV_REG = 20,   /* fused lowering in the register kernels, in the shape the rule picks */
+    CRISP_SHAPE_CONV_FORWARD = 21 /* the fused kernel crisp_conv_forward runs; EUNSUPPORTED where it runs none */
 };
 enum {
     CRISP_KERNEL_REG = 1, CRISP_KERNEL_GENERIC = 2, CRISP_KERNEL_LDS = 3, CRISP_KERNEL_XRES = 4,

@@ -244,6 +244,7 @@ def crisp_conv_spmm_ep(desc, conv: ConvDesc, row_ptr, col_idx, vals, idx_words, 
 
 
 SHAPE_AUTO = -1
+SHAPE_CONV_FORWARD = 21     # the fused kernel that crisp_conv_forward runs
 KERNEL_FAMILIES = {1: "reg", 2: "generic", 3: "lds", 4: "xres", 5: "conv_lds", 6: "conv_patch", 7: "b16", 8: "balanced", 9: "k8", 10: "xlds"}
 
 
@@ -324,6 +325,13 @@ class HipEvents:
         for a, b in self.pairs:
             self.hip.hipEventDestroy(a)
             self.hip.hipEventDestroy(b)
+
+
+def record_event(event, stream=-1):
+    """Records a raw hipEvent_t (see HipEvents) on a stream, the current one by default."""
+    hip = C.CDLL("libamdhip64.so")
+    if hip.hipEventRecord(C.c_void_p(getattr(event, "value", event)), C.c_void_p(_stream() if stream == -1 else stream)) != 0:
+        raise RuntimeError("hipEventRecord failed")
 
 
 @dataclass

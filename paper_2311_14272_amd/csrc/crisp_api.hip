@@ -394,7 +394,7 @@ static crisp_status conv_spmm_impl(const crisp_layer_desc* desc, const crisp_con
     // shapes of the fused lowering that may be forced (anything else: the automatic choice)
     if (!((force_shape >= 0 && force_shape <= 3) || (force_shape >= 7 && force_shape <= 10) ||
           force_shape == CRISP_SHAPE_CONV_LDS || force_shape == CRISP_SHAPE_CONV_PATCH || force_shape == CRISP_SHAPE_XLDS ||
-          force_shape == CRISP_SHAPE_CONV_TILE))
+          force_shape == CRISP_SHAPE_CONV_TILE || force_shape == CRISP_SHAPE_CONV_REG))
         force_shape = -1;
     hipError_t e = launch_spmm(g, desc->block_density, desc->select_mode == CRISP_ROW_UNIFORM, force_shape, row_ptr, col_idx, vals,
                                idx_words, act, conv,
@@ -447,14 +447,6 @@ crisp_status crisp_spmm_forced(const crisp_layer_desc* desc, const int32_t* row_
                      stream, nullptr, nullptr, ep);
 }
 
-crisp_status crisp_conv_spmm_forced(const crisp_layer_desc* desc, const crisp_conv_desc* conv, const int32_t* row_ptr,
-                                    const int32_t* col_idx, const uint16_t* vals, const uint32_t* idx_words,
-                                    const uint16_t* act, void* Y, int64_t ldy, int32_t y_dtype, const crisp_epilogue* ep,
-                                    int32_t shape, int32_t* kernel_code, void* stream) {
-    return conv_spmm_impl(desc, conv, row_ptr, col_idx, vals, idx_words, act, Y, ldy, y_dtype, shape, kernel_code, stream,
-                          nullptr, nullptr, ep);
-}
-
 // Thresholds of crisp_conv_plan, measured on the ResNet-50 shapes at batch 256.  A kept block gathered
 // with 2-byte loads costs about 0.8 of a block column of X written and read back once, the product over a
 // materialised X about 0.2 per kept block: the fused register kernels pay while block-rows x density (kept
@@ -503,6 +495,19 @@ static crisp_status conv_plan_impl(const crisp_layer_desc* desc, const crisp_con
     return CRISP_OK;
 }
 
+// Whether a fused kernel takes over from a planned materialised X because it is the faster one, and the shape it is forced
+// with: the kernel with a window of input positions (any number of columns), or the register kernels.
+static bool fused_instead_of_x(const crisp_layer_desc* desc, const Geometry& g, const crisp_conv_desc& conv, int64_t Ncol, int32_t* shape) {
+    const int64_t plane = (int64_t)conv.batch * conv.H * conv.W;
+    if (fused_lowering_covers(g, conv, Ncol, plane, true) && conv_tile_beats_im2col(g, desc->block_density, conv, Ncol)) {
+        *shape = CRISP_SHAPE_CONV_TILE;
+        return true;
+    }
+    *shape = CRISP_SHAPE_CONV_REG;
+    return desc->select_mode == CRISP_ROW_UNIFORM && fused_lowering_covers(g, conv, Ncol, plane) &&
+           conv_reg_beats_im2col(g, desc->block_density, conv, Ncol);
+}
+
 crisp_status crisp_conv_plan(const crisp_layer_desc* desc, const crisp_conv_desc* conv, int32_t* path, size_t* scratch_bytes) {
     if (!desc || !conv || !path) return CRISP_EINVAL;
     Geometry g;
@@ -510,6 +515,28 @@ crisp_status crisp_conv_plan(const crisp_layer_desc* desc, const crisp_conv_desc
     crisp_status st = conv_plan_impl(desc, conv, &g, path, &Ncol, &elems);
     if (st == CRISP_OK && scratch_bytes) *scratch_bytes = (size_t)elems * 2;
     return st;
+}
+
+crisp_status crisp_conv_spmm_forced(const crisp_layer_desc* desc, const crisp_conv_desc* conv, const int32_t* row_ptr,
+                                    const int32_t* col_idx, const uint16_t* vals, const uint32_t* idx_words,
+                                    const uint16_t* act, void* Y, int64_t ldy, int32_t y_dtype, const crisp_epilogue* ep,
+                                    int32_t shape, int32_t* kernel_code, void* stream) {
+    bool odd_ok = false;
+    if (shape == CRISP_SHAPE_CONV_FORWARD) {
+        if (!desc || !conv) return CRISP_EINVAL;
+        Geometry g;
+        int32_t path = 0;
+        int64_t Ncol = 0, elems = 0;
+        const crisp_status st = conv_plan_impl(desc, conv, &g, &path, &Ncol, &elems);
+        if (st != CRISP_OK) return st;
+        shape = CRISP_SHAPE_AUTO;
+        if (path != CRISP_CONV_FUSED) {
+            if (path != CRISP_CONV_IM2COL || !fused_instead_of_x(desc, g, *conv, Ncol, &shape)) return CRISP_EUNSUPPORTED;
+            odd_ok = true;
+        }
+    }
+    return conv_spmm_impl(desc, conv, row_ptr, col_idx, vals, idx_words, act, Y, ldy, y_dtype, shape, kernel_code, stream,
+                          nullptr, nullptr, ep, odd_ok);
 }
 
 crisp_status crisp_conv_forward(const crisp_layer_desc* desc, const crisp_conv_desc* conv, const int32_t* row_ptr,
@@ -535,16 +562,13 @@ crisp_status crisp_conv_forward(const crisp_layer_desc* desc, const crisp_conv_d
             if (path_taken) *path_taken = path;
             return CRISP_EBUFSIZE;
         }
-        const int64_t plane = (int64_t)conv->batch * conv->H * conv->W;
+        int32_t shape = CRISP_SHAPE_AUTO;
         if (ldy <= ((int64_t)1 << 23) && !(ep && ep->residual && ep->ldr > ((int64_t)1 << 23)) &&
-            !misaligned(x_scratch, 16) && !misaligned(row_ptr, 4) && !misaligned(col_idx, 4)) {
-            const bool tile = fused_lowering_covers(g, *conv, Ncol, plane, true) && conv_tile_beats_im2col(g, desc->block_density, *conv, Ncol);
-            if (tile || (desc->select_mode == CRISP_ROW_UNIFORM && fused_lowering_covers(g, *conv, Ncol, plane) &&
-                         conv_reg_beats_im2col(g, desc->block_density, *conv, Ncol))) {
-                if (path_taken) *path_taken = CRISP_CONV_FUSED;
-                return conv_spmm_impl(desc, conv, row_ptr, col_idx, vals, idx_words, act, Y, ldy, y_dtype,
-                                      tile ? CRISP_SHAPE_CONV_TILE : -1, nullptr, stream, nullptr, nullptr, ep, tile);
-            }
+            !misaligned(x_scratch, 16) && !misaligned(row_ptr, 4) && !misaligned(col_idx, 4) &&
+            fused_instead_of_x(desc, g, *conv, Ncol, &shape)) {
+            if (path_taken) *path_taken = CRISP_CONV_FUSED;
+            return conv_spmm_impl(desc, conv, row_ptr, col_idx, vals, idx_words, act, Y, ldy, y_dtype, shape, nullptr, stream,
+                                  nullptr, nullptr, ep, true);
         }
     }
     if (path_taken) *path_taken = path;

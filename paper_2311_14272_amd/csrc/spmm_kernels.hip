@@ -823,7 +823,8 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
     // forced shapes 7..10: shapes 0..3 of the register kernels with the sparse matrix-core instruction
     // (the automatic choice always takes it where the pattern is eligible: it was faster for every
     // measured layer; shapes 0..3 force the dense-expansion instantiations)
-    a.use_smf = (force_shape < 0 || force_shape == 13 || force_shape == CRISP_SHAPE_XLDS || (force_shape >= 7 && force_shape <= 10)) ? 1 : 0;
+    a.use_smf = (force_shape < 0 || force_shape == 13 || force_shape == CRISP_SHAPE_XLDS || force_shape == CRISP_SHAPE_CONV_REG ||
+                 (force_shape >= 7 && force_shape <= 10)) ? 1 : 0;
     // X-resident kernel for short K (forced shape 13).  Chosen for one block column, several
     // block-rows, patterns that go to the sparse matrix-core instruction and long X rows: 1.12x on the
     // 64 -> 256 channel layers of ResNet-50 at batch 256 (107 vs 120 us for 103 MB read and 411 MB
