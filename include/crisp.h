@@ -430,6 +430,7 @@ CRISP_API crisp_status crisp_conv_spmm_forced(const crisp_layer_desc *desc, cons
  * does not take); x_scratch may be NULL when no scratch is needed; with Y or residual
  * row strides above 2^23 a FUSED plan is run as IM2COL (then scratch of K x round_up(Ncol, 8) is needed
  * after all); *path_taken (optional, host) receives the way taken.
+ * Infinite elements of act: where X is planned, as crisp_spmm states for X, whichever way is taken.
  * Errors: those of the entry points named above; EBUFSIZE when the scratch is missing or too small.
  */
 enum { CRISP_CONV_DIRECT = 0, CRISP_CONV_FUSED = 1, CRISP_CONV_IM2COL = 2 };

@@ -281,6 +281,7 @@ void conv_tile_kernel(SpmmArgs p, ConvTileSched sc) {
                     u32x4 a4;
                     uint32_t idx;
                     smf_operand<N, M, B, s2>(av[rt], ws[rt], a4, idx);
+                    idx = smf_apart<N, M>(idx);
                     const bf16x8 afrag = __builtin_bit_cast(bf16x8, a4);
 #pragma unroll
                     for (int c = 0; c < NACC; ++c)

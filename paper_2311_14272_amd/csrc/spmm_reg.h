@@ -461,7 +461,8 @@ __device__ __forceinline__ void smf_operand(const uint32_t (&av)[Fmt<N, M, B>::K
 // one that belongs to the zero moves to a neighbouring column (a zero of the upper four of a 2:8 group stands first, every
 // other one second).  An infinite element of X at a kept column is then multiplied by its weight alone and not also by
 // zero; at a dropped column of a kept block the product is NaN or left out, as a dense expansion would have it NaN.
-// Six integer operations per operand at most; the ragged kernels alone do this, which took over from the generic one.
+// Six integer operations per operand at most; the kernels do this that run in place of the generic one or of the product
+// over a materialised X of any size: the ragged ones, and the convolutions but for those whose pairs come from one load.
 template <int N, int M>
 __device__ __forceinline__ uint32_t smf_apart(uint32_t idx) {
     if constexpr (N == 1) return idx ^ 0x4444u;
@@ -736,7 +737,7 @@ struct BlockBody {
             u32x4 a4;
             uint32_t idx;
             smf_operand<N, M, B, s2>(av[rt], ws[rt], a4, idx);
-            if constexpr (CONV == 6) idx = smf_apart<N, M>(idx);
+            if constexpr (CONV == 6 || (CONV >= 2 && CONV <= 4)) idx = smf_apart<N, M>(idx);
             const bf16x8 afrag = __builtin_bit_cast(bf16x8, a4);
 #pragma unroll
             for (int c = 0; c < NACC; ++c) {

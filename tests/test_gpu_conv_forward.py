@@ -66,3 +66,41 @@ def test_few_channels_in_the_register_kernels(shape):
     ref = c.through_x()
     # exact products in fp32, in another order: at most K roundings of 2^-24 of the sum of the magnitudes (0.1 each)
     assert float((out - ref).abs().max()) <= 2.0 ** -24 * c.cv.K * (c.W.view(torch.bfloat16).float().abs().sum(1).max().item() * 5 + 1)
+
+
+def _infinities(act):
+    """Few infinite elements, of both signs, none two in one filter window of the same image where images are large."""
+    flat = act.view(act.shape[0], act.shape[1], -1)
+    for c in range(0, flat.shape[0], 7):
+        flat[c, c % flat.shape[1], (c * 37 + 5) % flat.shape[2]] = float("inf") if c % 2 else float("-inf")
+
+
+@pytest.mark.parametrize("n,m", [(1, 4), (2, 4), (3, 4), (1, 8), (2, 8), (4, 8)])
+@pytest.mark.parametrize("shape,family", [
+    ((96, 128, 13, 13, 45, 3, 1, 1, 64, 1.0), "conv_lds"),     # odd number of columns
+    ((64, 72, 33, 33, 13, 3, 1, 1, 64, 1.0), "conv_lds"),      # ... channels that are no multiple of the block edge
+    ((40, 64, 7, 7, 301, 5, 1, 2, 32, 1.0), "conv_lds"),
+    ((512, 40, 18, 18, 90, 3, 2, 1, 64, 1.0), "conv_lds"),     # K no multiple of 16
+    ((160, 72, 13, 13, 2, 1, 2, 0, 64, 1.0), "reg"),           # strided, one tap: rows located one by one
+    ((160, 27, 13, 13, 2, 1, 2, 0, 64, 1.0), "reg"),           # ... with a short last group
+    ((192, 64, 13, 13, 2, 1, 2, 0, 64, 1.0), "reg"),           # columns one by one
+    ((1100, 128, 10, 4, 3, 1, 2, 0, 64, 1.0), "reg"),          # pairs from one 8-byte piece
+    ((300, 96, 13, 13, 2, 1, 2, 0, 32, 0.7), "reg"),
+    ((192, 64, 13, 13, 2, 3, 2, 1, 64, 0.6), "reg"),           # several taps
+], ids=str)
+def test_infinite_activations(shape, family, n, m):
+    """Convolutions whose K is no multiple of 16 or whose column count is none of four: wherever the product over X (generic
+    kernel) is a number or an infinity, the fused kernel that runs in its place has the same infinity, or a number within the
+    bound of the sums' order."""
+    S, C, H, W, batch, k, stride, pad, B, dens = shape
+    c = Conv(S, C, H, W, batch, k, stride, pad, n, m, B, dens, act=_infinities)
+    assert c.plan == "im2col" and (c.cv.K % 16 or c.N % 4)
+    out, way, ran = c.forward()
+    ref = c.through_x()
+    inf, fin = torch.isinf(ref), torch.isfinite(ref)
+    print(shape, n, m, way, ran, int(inf.sum()), int((out[inf] != ref[inf]).sum()), flush=True)
+    assert bool(inf.any()) and bool(fin.any())
+    assert torch.equal(out[inf], ref[inf]), "%s: %d of %d infinities lost" % (ran, int((out[inf] != ref[inf]).sum()), int(inf.sum()))
+    bound = 2.0 ** -24 * c.cv.K * (c.W.view(torch.bfloat16).float().abs().sum(1).max().item() * 5 + 1)
+    assert float((out[fin] - ref[fin]).abs().max()) <= bound
+    assert ran == family or (ran is None and (n, m) not in ((1, 4), (2, 8)))       # dense patterns may stay with X
