@@ -30,7 +30,7 @@ __device__ __forceinline__ int divide(int n, DivBy d) { return d.m ? (int)(__umu
 // not there: zeros), and each 16-deep step forms its own addresses from it.  A block is walked in every chunk it has a
 // part in.
 template <int N, int M, int B, int NC2, bool SMF, bool SPAN>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NC2 == 2 ? 2 : 3, NC2 == 2 ? 2 : 4)))
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(conv_tile_waves(N, M, B, NC2) / 4, NC2 == 2 ? 2 : 4)))
 void conv_tile_kernel(SpmmArgs p, ConvTileSched sc) {
     typedef Fmt<N, M, B> F;
     constexpr int RT = F::RT, KS = F::KS, NACC = 2 * NC2;
@@ -230,7 +230,7 @@ void conv_tile_kernel(SpmmArgs p, ConvTileSched sc) {
             for (int r = 0; r < 16; ++r) acc[rt][c][r] = 0.0f;
 
     // one kept block
-    auto multiply = [&](const uint32_t (&av)[RT][KS][F::VW], const uint32_t (&aw)[RT][F::WPR], uint32_t what, uint32_t off) __attribute__((always_inline)) {
+    auto multiply = [&](uint32_t (&av)[RT][KS][F::VW], const uint32_t (&aw)[RT][F::WPR], uint32_t what, uint32_t off) __attribute__((always_inline)) {
         uint32_t ws[RT][F::WPR];
         if constexpr (N != M) {
 #pragma unroll
@@ -255,6 +255,21 @@ void conv_tile_kernel(SpmmArgs p, ConvTileSched sc) {
         if constexpr (SPAN) {
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) oct[ks] = octets[off + ks * 2 + hh];
+            // Several chunks: weights whose K-rows are not in this one count in another.  They are cleared here, as an
+            // infinite one times the zeros that stand for its rows would be NaN.  (A lane's values av[..][ks] belong to octet
+            // 2 ks + hh, as sparse operands to the two neighbouring octets of its sixteen columns.  Once per block on the
+            // packed values: as part of each operand it cost 1.5 % of every case, one chunk or more.)
+            if (sc.chunks > 1) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const uint32_t o = SMF ? octets[off + (ks & ~1) * 2 + hh * 2 + (ks & 1)] : oct[ks];
+                    const uint32_t here = (o >> 20 & 31u) == 31u ? 0u : 0xFFFFFFFFu;
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                        for (int x = 0; x < F::VW; ++x) av[rt][ks][x] &= here;
+                }
+            }
         }
         auto rows_at = [&](int c, int ks) __attribute__((always_inline)) {
             if constexpr (SPAN) {

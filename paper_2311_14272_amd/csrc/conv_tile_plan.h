@@ -133,13 +133,18 @@ inline bool conv_tile_covers(const ConvShape& a) {
            a.pad < a.kh && a.plane < ((int64_t)1 << 26) && a.Ncol < ((int64_t)1 << 30);
 }
 
+// Waves of a compute unit that the kernel's registers leave room for.  2:4 with 64x64 blocks has two packed slices of 20
+// registers on their way: three waves per SIMD would spill 14 to 54 of 168 registers (256 x 10400 x 20384: 190 us, with two
+// waves 104; fifteen such convolutions with channels that are no multiple of 64 at 0.57 of the time, twenty others at 0.98).
+constexpr int conv_tile_waves(int n, int m, int B, int NC2) { return NC2 == 2 || (n == 2 && m == 4 && B == 64) ? 8 : 12; }
+
 // Estimated time of a schedule in clocks of a compute unit (bpr: kept blocks per block-row; bf16 outputs, so that the choice
 // and with it the order of the sums is the same for both output types).  A workgroup's phases follow
 // one another: window in (9 bytes per clock and compute unit when all stage at once: 5 TB/s), blocks, rows out; two and
 // more workgroups of a compute unit overlap theirs.
 inline double conv_tile_cost(const ConvShape& a, const ConvTileSched& s, int bpr) {
     const int waves = s.RG * s.PT;
-    const int fit = 160 * 1024 / (s.lds_bytes + 4352), room = (s.NC2 == 2 ? 8 : 12) / waves;
+    const int fit = 160 * 1024 / (s.lds_bytes + 4352), room = conv_tile_waves(a.n, a.m, a.B, s.NC2) / waves;
     const int per_cu = fit < room ? fit : room;
     const int wgs = s.tiles * s.row_groups;
     const double matrix = (a.n <= 2 ? 256.0 : 512.0) * s.NC2 * (a.B == 64 ? 1.0 : 0.25);

@@ -104,3 +104,32 @@ def test_infinite_activations(shape, family, n, m):
     bound = 2.0 ** -24 * c.cv.K * (c.W.view(torch.bfloat16).float().abs().sum(1).max().item() * 5 + 1)
     assert float((out[fin] - ref[fin]).abs().max()) <= bound
     assert ran == family or (ran is None and (n, m) not in ((1, 4), (2, 8)))       # dense patterns may stay with X
+
+
+@pytest.mark.parametrize("n,m", [(1, 4), (2, 4), (3, 4), (4, 4), (1, 8), (2, 8), (4, 8), (8, 8)])
+@pytest.mark.parametrize("shape", [(300, 272, 28, 28, 2, 3, 2, 0, 64, 1.0), (70, 400, 16, 16, 2, 3, 1, 0, 32, 1.0)], ids=str)
+def test_infinite_weights_over_several_chunks(shape, n, m):
+    """Channels in several chunks, block columns of several taps: an infinite weight meets its own activations only, whatever
+    chunk its block is walked in."""
+    S, C, H, W, batch, k, stride, pad, B, dens = shape
+
+    def weight(Wf):
+        for i in range(0, Wf.shape[0], 3):
+            Wf[i, (i * 131 + 17) % Wf.shape[1]] = float("inf") if i % 2 else float("-inf")
+
+    c = Conv(S, C, H, W, batch, k, stride, pad, n, m, B, dens, weight=weight)
+    y, ref = c.layer, c.through_x()
+    Y = torch.full((S, c.ld), float("nan"), dtype=torch.float32, device="cuda")
+    code = crisp.crisp_conv_spmm_forced(y.desc, crisp.conv_desc_of(c.cv), y.row_ptr, y.col_idx, y.vals, y.idx_words, c.act, Y, c.ld,
+                                        crisp.Y_F32, None, 19)
+    torch.cuda.synchronize()
+    f = crisp.kernel_code_fields(code)
+    assert f["family"] == "conv_lds" and f["shape"] in (1, 2)
+    out = Y[:, :c.N]
+    inf, fin = torch.isinf(ref), torch.isfinite(ref)
+    print(shape, n, m, int(inf.sum()), int(torch.isnan(out[inf]).sum()), flush=True)
+    assert bool(inf.any()) and bool(fin.any()) and not bool(torch.isnan(ref).any())
+    assert torch.equal(out[inf], ref[inf]), "%d of %d infinities lost" % (int((out[inf] != ref[inf]).sum()), int(inf.sum()))
+    rows = c.W.view(torch.bfloat16).float().abs()
+    bound = 2.0 ** -24 * c.cv.K * (rows[torch.isfinite(rows).all(1)].sum(1).max().item() * 5 + 1)
+    assert float((out[fin] - ref[fin]).abs().max()) <= bound
