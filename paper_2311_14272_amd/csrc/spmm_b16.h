@@ -12,6 +12,7 @@
 // at a time without anything requested ahead, 64 columns per wave (before / now): 64 x 2144 x 125200 3:4 241 / 147 us (2.9 / 4.8
 // TB/s), 64 x 3840 x 1173 1:4 88 / 10.5 us, 1408 x 4416 x 5520 4:8 618 / 162 us.
 #pragma once
+#include "packed_addr.h"
 #include "spmm_reg.h"
 
 namespace crisp {
@@ -72,8 +73,8 @@ void spmm_b16_pair_kernel(SpmmArgs p) {
             }
         }
         const rsrc_t rv = make_rsrc(p.vals), ri = make_rsrc(p.idxw);
-        load_vals<F::FS>(rv, (uint32_t)(((t * 16 + j) * F::SLOTS + half * F::FS) * 2), 0, av[d]);
-        if constexpr (N != M) load_positions<F::WPR>(ri, (uint32_t)((t * 16 + j) * F::WPR * 4), 0, aw[d]);
+        load_vals<F::FS>(rv, b16_value_at(t, j, F::SLOTS, half * F::FS), 0, av[d]);
+        if constexpr (N != M) load_positions<F::WPR>(ri, b16_words_at(t, j, F::WPR), 0, aw[d]);
     };
     auto multiply = [&](int d) __attribute__((always_inline)) {
         // a list of odd length: the last pair's second block is zero in both operands (an infinite element of X times a
