@@ -138,19 +138,30 @@ inline bool conv_tile_covers(const ConvShape& a) {
 // waves 104; fifteen such convolutions with channels that are no multiple of 64 at 0.57 of the time, twenty others at 0.98).
 constexpr int conv_tile_waves(int n, int m, int B, int NC2) { return NC2 == 2 || (n == 2 && m == 4 && B == 64) ? 8 : 12; }
 
-// Estimated time of a schedule in clocks of a compute unit (bpr: kept blocks per block-row; bf16 outputs, so that the choice
-// and with it the order of the sums is the same for both output types).  A workgroup's phases follow
-// one another: window in (9 bytes per clock and compute unit when all stage at once: 5 TB/s), blocks, rows out; two and
-// more workgroups of a compute unit overlap theirs.
+// What a schedule has a compute unit do, in clocks.
+struct ConvTileClocks {
+    int waves, per_cu;       // waves of a workgroup, workgroups of a compute unit
+    double matrix, vector;   // of one kept block in one wave
+};
+inline ConvTileClocks conv_tile_clocks(const ConvShape& a, const ConvTileSched& s) {
+    ConvTileClocks c;
+    c.waves = s.RG * s.PT;
+    const int fit = 160 * 1024 / (s.lds_bytes + 4352), room = conv_tile_waves(a.n, a.m, a.B, s.NC2) / c.waves;
+    c.per_cu = fit < room ? fit : room;
+    c.matrix = (a.n <= 2 ? 256.0 : 512.0) * s.NC2 * (a.B == 64 ? 1.0 : 0.25);
+    c.vector = (a.n == 3 ? 1300.0 : a.n == 4 && a.m == 8 ? 450.0 : a.n == 2 && a.m == 8 ? 430.0 : 200.0) * (a.B == 64 ? 1.0 : 0.3) + 60.0 * s.NC2 +
+               (s.octets ? (a.B == 64 ? 128.0 : 64.0) * s.NC2 : 0.0);
+    return c;
+}
+
+// Estimated time of a schedule in clocks of a compute unit, by which one of them is chosen (bpr: kept blocks per block-row;
+// bf16 outputs, so that the choice and with it the order of the sums is the same for both output types).  A workgroup's
+// phases follow one another: window in (9 bytes per clock and compute unit when all stage at once: 5 TB/s), blocks, rows
+// out; two and more workgroups of a compute unit overlap theirs.
 inline double conv_tile_cost(const ConvShape& a, const ConvTileSched& s, int bpr) {
-    const int waves = s.RG * s.PT;
-    const int fit = 160 * 1024 / (s.lds_bytes + 4352), room = conv_tile_waves(a.n, a.m, a.B, s.NC2) / waves;
-    const int per_cu = fit < room ? fit : room;
-    const int wgs = s.tiles * s.row_groups;
-    const double matrix = (a.n <= 2 ? 256.0 : 512.0) * s.NC2 * (a.B == 64 ? 1.0 : 0.25);
-    const double vector = (a.n == 3 ? 1300.0 : a.n == 4 && a.m == 8 ? 450.0 : a.n == 2 && a.m == 8 ? 430.0 : 200.0) * (a.B == 64 ? 1.0 : 0.3) + 60.0 * s.NC2 +
-                          (s.octets ? (a.B == 64 ? 128.0 : 64.0) * s.NC2 : 0.0);
-    const double block = waves / 4.0 * (matrix + 0.5 * vector);
+    const ConvTileClocks c = conv_tile_clocks(a, s);
+    const int per_cu = c.per_cu, wgs = s.tiles * s.row_groups;
+    const double block = c.waves / 4.0 * (c.matrix + 0.5 * c.vector);
     const double in = 2.0 * s.HP * a.C * 2 / 9.0 + 3000.0 * s.chunks;
     const double out = (double)(s.RG < a.Sb ? s.RG : a.Sb) * a.B * s.TC * 2 / 9.0;
     const double walk = bpr * block * (1.0 + 0.12 * (s.chunks - 1)) * (s.octets && s.chunks > 1 ? 1.0 + (double)a.B / s.CC : 1.0);
@@ -186,35 +197,6 @@ inline bool conv_tile_choose(const ConvShape& a, int bpr, ConvTileSched* out, do
     if (best == 0.0) return false;
     out->by_Wo = div_by(a.Wo); out->by_Ho = div_by(a.Ho); out->by_unit = div_by(out->per_unit);
     return true;
-}
-
-// What would run instead.
-enum ConvTileRival { RIVAL_FUSED = 0, RIVAL_PATCH = 1, RIVAL_IM2COL = 2 };
-
-// Whether it is the faster choice, in microseconds.  bt: kept blocks x 64 columns per compute unit (a 32 x 32 block counts a
-// third).  Channel counts that are multiples of the block edge: against the register kernels, the kernel that stages whole
-// output rows (conv_lds.h) and a materialised X, 10 for a launch and a block list plus, per bt, 0.4 where column pairs
-// come from one load and 1.3 where columns are located one by one.  Over 300 random convolutions (3x3 and 5x5, stride 1
-// and 2, 32 to 512 channels, images of 7x7 to 56x56, batch 1 to 256, all patterns, both block sizes, densities 0.2 to
-// 0.8) the rule keeps all but 0.5 % of what the better of both gives each time (geometric mean 1.19 over the whole set,
-// up to 3.6) and is wrong by more than 3 % in four of them (up to 1.21: 144 x 2880 x 8134 3:4).
-// Other multiples of eight: the register kernels split every K-row into tap and channel (7, and 0.9 per bt and 0.7 per block
-// of the chain, 0.32 where it is 32 x 32: 193 random convolutions); the few-channel kernel takes 15 and more whatever the
-// size; a materialised X is written and read once (5 TB/s).  250 random convolutions run at 1.36 times the speed, geometric
-// mean (160 of them with 24 and more channels mostly: 1.41, 1.46 with the better of both each time); seven are slower by more
-// than 5 % (the worst by 1.15, and 1.42 for 256 x 9200 x 3136 2:4, 41 / 58 us, where X stays in the caches).
-// An odd number of columns has only the materialised X beside it: 120 random convolutions of the same ranges 1.61 times the
-// speed (368 x 2376 x 142659 1:4 656 / 203 us), seven of them slower by 3 to 8 %.
-// A strided 1x1 filter leaves out three quarters of what would be staged: 0.4-1.3, not taken.
-inline bool conv_tile_pays(const ConvShape& a, int bpr, double cost, ConvTileRival rival) {
-    if (a.kh * a.kw <= 1) return false;
-    const double us = cost / 2100.0 + 6.0;
-    const double bt = (double)a.Sb * (double)((a.Ncol + 63) / 64) * bpr / 256.0 * (a.B == 64 ? 1.0 : 0.3);
-    if (rival == RIVAL_IM2COL && us < 13.0 + bt * 0.3 + 1.5 * 4e-6 / 5.0 * ((double)a.kh * a.kw * a.C) * (double)a.Ncol) return true;
-    if (a.C % a.B == 0) return us < 10.0 + bt * (a.stride == 1 ? 0.4 : 1.3);
-    if (rival == RIVAL_PATCH) return us < 15.0 + bt * 0.3;
-    if (rival == RIVAL_IM2COL) return false;
-    return us * 1.03 < 7.0 + bt * 0.9 + bpr * (a.B == 64 ? 0.7 : 0.32);
 }
 
 }  // namespace crisp

@@ -499,13 +499,10 @@ static crisp_status conv_plan_impl(const crisp_layer_desc* desc, const crisp_con
 // with: the kernel with a window of input positions (any number of columns), or the register kernels.
 static bool fused_instead_of_x(const crisp_layer_desc* desc, const Geometry& g, const crisp_conv_desc& conv, int64_t Ncol, int32_t* shape) {
     const int64_t plane = (int64_t)conv.batch * conv.H * conv.W;
-    if (fused_lowering_covers(g, conv, Ncol, plane, true) && conv_tile_beats_im2col(g, desc->block_density, conv, Ncol)) {
-        *shape = CRISP_SHAPE_CONV_TILE;
-        return true;
-    }
-    *shape = CRISP_SHAPE_CONV_REG;
-    return desc->select_mode == CRISP_ROW_UNIFORM && fused_lowering_covers(g, conv, Ncol, plane) &&
-           conv_reg_beats_im2col(g, desc->block_density, conv, Ncol);
+    if (!fused_lowering_covers(g, conv, Ncol, plane, true)) return false;
+    *shape = conv_instead_of_x(g, desc->block_density, desc->select_mode == CRISP_ROW_UNIFORM, conv, Ncol,
+                               fused_lowering_covers(g, conv, Ncol, plane));
+    return *shape != CRISP_SHAPE_AUTO;
 }
 
 crisp_status crisp_conv_plan(const crisp_layer_desc* desc, const crisp_conv_desc* conv, int32_t* path, size_t* scratch_bytes) {

@@ -48,11 +48,10 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
 
 // Whether launch_spmm would run this convolution with the input patch staged in LDS (host only).
 bool conv_lds_suits(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol);
-// Whether the kernel that runs it from a window of input positions in LDS (CRISP_SHAPE_CONV_TILE) is expected to be faster
-// than a materialised X.
-bool conv_tile_beats_im2col(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol);
-// Whether the fused register kernels are, for a convolution that they cover (rows of equal block counts).
-bool conv_reg_beats_im2col(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol);
+// The fused kernel that runs in place of a planned materialised X, as the shape it is forced with: CRISP_SHAPE_CONV_TILE,
+// CRISP_SHAPE_CONV_REG, or CRISP_SHAPE_AUTO for none.  reg_covers: the register kernels take this convolution.
+int conv_instead_of_x(const Geometry& g, double density_hint, bool uniform_rows, const crisp_conv_desc& conv, int64_t Ncol,
+                      bool reg_covers);
 bool xlds_conv_would_run(const Geometry& g, const crisp_conv_desc& conv, int64_t Ncol);
 
 #define CRISP_BUDGET_MAX_LAYERS 64

@@ -8,6 +8,7 @@
 // the benchmark workloads use have register-resident specialisations (spmm_reg.h), which the
 // dispatcher prefers.
 #include "conv_lds.h"
+#include "conv_ways.h"
 
 namespace crisp {
 
@@ -597,50 +598,48 @@ static int blocks_per_row(const Geometry& g, double density_hint) {
     return bpr < 1 ? 1 : bpr;
 }
 
-// Schedule of the convolution kernel with a window of input positions in LDS and its estimated time; false where it does
-// not apply.
-static bool conv_tile_schedule(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol, ConvShape* c,
-                               ConvTileSched* s, double* cost) {
+static void conv_shape_of(const Geometry& g, const crisp_conv_desc& conv, int64_t Ncol, ConvShape* c) {
     c->Sb = g.Sb; c->n = g.n; c->m = g.m; c->B = g.B; c->Kb = g.Kb;
     c->Ncol = Ncol; c->plane = (int64_t)conv.batch * conv.H * conv.W;
     c->C = conv.C; c->H = conv.H; c->W = conv.W; c->kh = conv.kh; c->kw = conv.kw; c->stride = conv.stride; c->pad = conv.pad;
     c->Ho = (conv.H + 2 * conv.pad - conv.kh) / conv.stride + 1;
     c->Wo = (conv.W + 2 * conv.pad - conv.kw) / conv.stride + 1;
+}
+
+// Schedule of the convolution kernel with a window of input positions in LDS; false where it does not apply.
+static bool conv_tile_schedule(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol, ConvShape* c,
+                               ConvTileSched* s, double* cost) {
+    conv_shape_of(g, conv, Ncol, c);
     return conv_tile_covers(*c) && conv_tile_choose(*c, blocks_per_row(g, density_hint), s, cost);
 }
 
-bool conv_tile_beats_im2col(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol) {
+// Strided convolutions, odd numbers of columns and others are planned through a materialised X; where a fused kernel is
+// estimated to be ahead of it (conv_ways.h), that one runs.  The register kernels locate every column again for each kept
+// block and wait for 2-byte loads down the list: filters of several taps and channels that are no multiple of the block edge
+// go there with up to 8 blocks a row (longer lists gain 7 % on average, and lose as much now and then), and rows of equal
+// length only.
+int conv_instead_of_x(const Geometry& g, double density_hint, bool uniform_rows, const crisp_conv_desc& conv, int64_t Ncol,
+                      bool reg_covers) {
+    const int bpr = blocks_per_row(g, density_hint);
+    const bool sparse = g.n <= 2, one_tap = conv.kh * conv.kw == 1;
     ConvShape c;
     ConvTileSched s;
-    double cost = 0.0;
-    return conv.kh * conv.kw > 1 && conv_tile_schedule(g, density_hint, conv, Ncol, &c, &s, &cost) &&
-           conv_tile_pays(c, blocks_per_row(g, density_hint), cost, RIVAL_IM2COL);
-}
-
-// Microseconds, fitted to 380 random convolutions that are planned through a materialised X (strided 1x1, 3x3 and 5x5, images
-// of 7x7 to 56x56, batch 1 to 256, 32 to 1024 channels, of them 110 no multiple of the block edge; all patterns, both block
-// sizes, densities 0.2 to 0.8); bt: kept blocks x 64 columns per compute unit, bq: blocks of a row (a 32 x 32 block counts a
-// third and a half).  Materialising costs a second launch and the write and read of X; the register kernels locate every
-// column again for each kept block (an 8-byte piece per pair in a strided 1x1 filter of even widths) and wait for 2-byte loads
-// down the list, so filters of several taps and channels that are no multiple of the block edge come here with up to 8 blocks
-// a row: longer lists gain 7 % on average, and lose as much now and then.  160 x 704 x 1176 2:4 10.6 / 5.9 us,
-// 1792 x 256 x 1400 4:8 13.7 / 9.5, 320 x 576 x 3332 3:4 14.9 / 9.6; against it 592 x 896 x 4624 3:4 38.4 / 70.9,
-// 144 x 8352 x 352 1:4 29.8 / 47.8.  Geometric mean 1.24 over the 380, three slower by 8 to 17 %.
-bool conv_reg_beats_im2col(const Geometry& g, double density_hint, const crisp_conv_desc& conv, int64_t Ncol) {
+    double clocks = 0.0, best = -1.0;
+    int shape = CRISP_SHAPE_AUTO;
     SpmmArgs a{};
     fill_conv_args(a, g, conv);
-    const int bpr = blocks_per_row(g, density_hint);
-    const bool one_tap = conv.kh * conv.kw == 1, spans = a.conv_mode == 3;
-    if ((spans || !one_tap) && bpr > 8) return false;
-    const double bt = (double)g.Sb * (double)((Ncol + 63) / 64) * bpr / 256.0 * (g.B == 64 ? 1.0 : 0.3);
-    const double bq = bpr * (g.B == 64 ? 1.0 : 0.5);
-    const double x_us = 4e-6 / 5.0 * (double)g.K * (double)Ncol;                  // X written and read at 5 TB/s
-    const double fused = spans                ? 6.5 + 0.75 * bt + 0.75 * bq
-                         : a.conv_mode == 4   ? 6.0 + 0.7 * bt
-                         : one_tap            ? 5.7 + 1.25 * bt + 0.08 * bq
-                                              : 5.0 + 0.45 * bt + 0.45 * bq;
-    const double apart = one_tap ? 9.5 + 0.5 * bt + 0.06 * bq + 2.0 * x_us : 9.4 + 0.25 * bt + 0.25 * bq + 1.05 * x_us;
-    return fused * 1.1 < apart;
+    if (!one_tap && conv_tile_schedule(g, density_hint, conv, Ncol, &c, &s, &clocks)) {
+        best = conv_tile_us(c, s, bpr) * WINDOW_OVER_X * (uniform_rows ? 1.0 : WINDOW_UNEVEN);
+        shape = CRISP_SHAPE_CONV_TILE;
+    } else {
+        conv_shape_of(g, conv, Ncol, &c);
+    }
+    if (reg_covers && uniform_rows && (bpr <= 8 || (one_tap && a.conv_mode != 3))) {
+        const double us = conv_reg_us(c, bpr, pick_shape(g, Ncol, bpr, sparse) >= 2, a.conv_mode) * REG_OVER_X;
+        if (best < 0.0 || us < best) { best = us; shape = CRISP_SHAPE_CONV_REG; }
+    }
+    const bool x_sparse = sparse || g.two_of_four;
+    return best >= 0.0 && best < conv_x_us(c, bpr, pick_shape(g, Ncol, bpr, x_sparse) >= 2, x_sparse) ? shape : CRISP_SHAPE_AUTO;
 }
 
 hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows, int force_shape, const int32_t* row_ptr,
@@ -714,13 +713,28 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
     ConvPatchSched ps;
     const bool patch_ok = conv && (force_shape == 14 || force_shape < 0) && ld_wide <= ((int64_t)1 << 23) &&
                           conv_patch_plan(a, g.B, conv->kh, g.Kb, &ps);
-    // convolution from a window of input positions in LDS (forced shape 19)
+    // convolution with the input patch staged in LDS, a patch of whole output rows (forced shape 12)
+    ConvLdsSched cs;
+    const bool conv_lds_ok = conv && (force_shape == 12 || force_shape < 0) && (Ncol % 4) == 0 && ld_wide <= ((int64_t)1 << 23) &&
+                             conv_lds_plan(a, g.B, conv->kh, &cs) &&
+                             (force_shape == 12 || conv_lds_pays(cs, a, density_hint, conv->batch, g.n <= 2));
+    // or from a window of input positions (forced shape 19): where it is estimated to be ahead of what runs otherwise
     ConvTileSched ts;
     ConvShape tshape;
-    double tcost = 0.0;
-    if (conv && (force_shape == CRISP_SHAPE_CONV_TILE || (force_shape < 0 && conv->kh * conv->kw > 1)) && ld_wide <= ((int64_t)1 << 23) &&
-        conv_tile_schedule(g, density_hint, *conv, Ncol, &tshape, &ts, &tcost) &&
-        (force_shape >= 0 || conv_tile_pays(tshape, blocks_per_row(g, density_hint), tcost, patch_ok ? RIVAL_PATCH : RIVAL_FUSED))) {
+    double tclocks = 0.0;
+    auto window_ahead = [&] {
+        const int bpr = blocks_per_row(g, density_hint);
+        conv_shape_of(g, *conv, Ncol, &tshape);
+        const double other = conv_lds_ok ? conv_staged_us(tshape, bpr)
+                             : patch_ok  ? conv_patch_us(tshape, bpr)
+                                         : conv_reg_us(tshape, bpr, pick_shape(g, Ncol, bpr, g.n <= 2) >= 2, a.conv_mode);
+        const double margin = WINDOW_OVER_FUSED * (uniform_rows ? 1.0 : WINDOW_UNEVEN);
+        return WINDOW_LEAST_US * margin < other && conv_tile_schedule(g, density_hint, *conv, Ncol, &tshape, &ts, &tclocks) &&
+               conv_tile_us(tshape, ts, bpr) * margin < other;
+    };
+    if (conv && ld_wide <= ((int64_t)1 << 23) &&
+        (force_shape == CRISP_SHAPE_CONV_TILE ? conv_tile_schedule(g, density_hint, *conv, Ncol, &tshape, &ts, &tclocks)
+                                              : force_shape < 0 && conv->kh * conv->kw > 1 && window_ahead())) {
         report(CRISP_KERNEL_CONV_LDS, ts.NC2, a.conv_mode, g.n <= 2);
         switch (g.n * 16 + g.m) {
             case 1 * 16 + 4: return launch_conv_tile_nm<1, 4>(a, g.B, ts, st);
@@ -734,11 +748,7 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
             default: break;
         }
     }
-    // convolution with the input patch staged in LDS (forced shape 12)
-    ConvLdsSched cs;
-    const bool conv_lds_wanted = force_shape == 12 || force_shape < 0;
-    if (conv && conv_lds_wanted && (Ncol % 4) == 0 && ld_wide <= ((int64_t)1 << 23) && conv_lds_plan(a, g.B, conv->kh, &cs) &&
-        (force_shape == 12 || conv_lds_pays(cs, a, density_hint, conv->batch, g.n <= 2))) {
+    if (conv_lds_ok) {
         a.use_smf = 1;
         report(CRISP_KERNEL_CONV_LDS, 0, a.conv_mode, g.n <= 2);
         switch (g.n * 16 + g.m) {

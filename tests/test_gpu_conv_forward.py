@@ -81,7 +81,7 @@ def _infinities(act):
     ((64, 72, 33, 33, 13, 3, 1, 1, 64, 1.0), "conv_lds"),      # ... channels that are no multiple of the block edge
     ((40, 64, 7, 7, 301, 5, 1, 2, 32, 1.0), "conv_lds"),
     ((512, 40, 18, 18, 90, 3, 2, 1, 64, 1.0), "conv_lds"),     # K no multiple of 16
-    ((160, 72, 13, 13, 2, 1, 2, 0, 64, 1.0), "reg"),           # strided, one tap: rows located one by one
+    ((320, 40, 13, 13, 2, 1, 2, 0, 64, 1.0), "reg"),           # strided, one tap: rows located one by one
     ((160, 27, 13, 13, 2, 1, 2, 0, 64, 1.0), "reg"),           # ... with a short last group
     ((192, 64, 13, 13, 2, 1, 2, 0, 64, 1.0), "reg"),           # columns one by one
     ((1100, 128, 10, 4, 3, 1, 2, 0, 64, 1.0), "reg"),          # pairs from one 8-byte piece
@@ -133,3 +133,35 @@ def test_infinite_weights_over_several_chunks(shape, n, m):
     rows = c.W.view(torch.bfloat16).float().abs()
     bound = 2.0 ** -24 * c.cv.K * (rows[torch.isfinite(rows).all(1)].sum(1).max().item() * 5 + 1)
     assert float((out[fin] - ref[fin]).abs().max()) <= bound
+
+
+# us of the ways: through X, from a window, in the register kernels
+@pytest.mark.parametrize("shape,uneven,expect", [
+    ((256, 464, 28, 28, 3, 5, 1, 2, 1, 4, 32, 0.70), 0, "im2col"),    # 62 / 100 / 149
+    ((75, 304, 20, 20, 3, 1, 2, 0, 4, 8, 64, 0.47), 0, "im2col"),     # 8.8 / - / 12.8
+    ((195, 352, 28, 28, 20, 5, 2, 2, 1, 4, 64, 0.47), 1, "im2col"),   # 57 / 84 / 129, block-rows of any length
+    ((794, 384, 33, 33, 4, 3, 2, 1, 3, 4, 64, 0.77), 1, "im2col"),    # 42 / 65 / 102
+    ((508, 64, 20, 20, 18, 3, 2, 1, 2, 4, 64, 0.77), 0, "reg"),       # planned fused: - / 15 / 8.1
+    ((256, 192, 20, 20, 18, 5, 1, 2, 2, 8, 64, 0.32), 0, "reg"),      # - / 26.5 / 16.5
+    ((512, 512, 14, 14, 256, 3, 2, 1, 4, 8, 64, 0.40), 0, "conv_lds"),   # 130 / 55 / -
+    ((256, 256, 14, 14, 256, 3, 1, 1, 2, 8, 64, 0.60), 0, "conv_lds"),   # - / 39 / 47
+    ((64, 64, 33, 33, 119, 3, 1, 1, 4, 8, 64, 0.281), 1, "conv_lds"),    # 67 / 17 / -, block-rows of any length
+], ids=str)
+def test_the_faster_way_is_taken(shape, uneven, expect):
+    """Convolutions that once took the slower way by a third and more, and some that are well ahead in the window kernel."""
+    S, C, H, W, batch, k, stride, pad, n, m, B, dens = shape
+    cv = synth.ConvShape(C, H, W, batch, k, k, stride, pad)
+    layer = crisp.alloc_layer(crisp.layer_desc(S, cv.K, n, m, B, dens, crisp.SAL_MAG, crisp.LAYER_TOPK if uneven else crisp.ROW_UNIFORM))
+    g = torch.Generator(device="cuda").manual_seed(1)
+    crisp.prune_and_pack(layer, torch.randn((S, cv.K), generator=g, device="cuda").to(torch.bfloat16).view(torch.int16), None)
+    act = torch.randn((C, batch, H, W), generator=g, device="cuda").to(torch.bfloat16).view(torch.int16)
+    ld = (cv.Ncol + 7) // 8 * 8
+    X = torch.empty(max(8, crisp.conv_plan(layer.desc, cv)[1] // 2), dtype=torch.int16, device="cuda")
+    Y = torch.empty((S, ld), dtype=torch.bfloat16, device="cuda")
+    way = crisp.conv_forward(layer, cv, act, Y, ld, crisp.Y_BF16, X)
+    if way == "fused":
+        code = crisp.crisp_conv_spmm_forced(layer.desc, crisp.conv_desc_of(cv), layer.row_ptr, layer.col_idx, layer.vals, layer.idx_words,
+                                            act, Y, ld, crisp.Y_BF16, None, crisp.SHAPE_CONV_FORWARD)
+        way = crisp.kernel_code_fields(code)["family"]
+    torch.cuda.synchronize()
+    assert way == expect
