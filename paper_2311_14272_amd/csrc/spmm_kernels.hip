@@ -896,12 +896,19 @@ hipError_t launch_spmm(const Geometry& g, double density_hint, bool uniform_rows
     // blocks or patterns of dense expansion, 0.4 in the middle (512 x 2305 x 50003 2:4, 64x64 blocks: 130 against 276
     // us).  With 32x32 blocks, the sparse instruction, many tiles and long rows the generic kernel's wide strips were ahead
     // while one block of X was in flight; with two in flight it is 0.38-1.02 over ninety such products (736 x 472 x 195752
-    // 1:4: 342 against 565 us), most with a layer tail, except for 1:8 without one on up to 3500 tiles (1.09-1.29: 699 x
-    // 4401 x 5100 59 against 48 us), which stays, as do 1:8 and very long rows with fp32 output (0.85-1.29, 0.97).
-    const int64_t tiles_r = (int64_t)g.Sb * ((Ncol + 63) / 64);
+    // 1:4: 342 against 565 us), most with a layer tail, except without one for 1:8 on up to 3500 tiles (1.09-1.29: 699 x
+    // 4401 x 5100 59 against 48 us), which stays, as do 1:8 and very long rows with fp32 output (0.85-1.29, 0.97).  1:8 with
+    // rows of 15 and more blocks, with a tail or without: 1.07-1.35 where an XCD, whose share of the strips is whole, has
+    // more workgroups than fit its 32 compute units at two each and less than twice as many (24 products, two of them 0.87
+    // and 0.93; 64 x 4080 x 65793 130 against 104 us), 0.62-0.82 where it has no more; 1.02-1.11 from 16000 tiles and 45
+    // blocks on, 0.75-1.11 elsewhere.
+    const int64_t tiles_r = (int64_t)g.Sb * ((Ncol + 63) / 64), xcd_groups = (Ncol + 2047) / 2048 * g.Sb;
     const bool one_of_8 = 8 * g.n / g.m <= 1;
-    const bool generic_b32 = g.B == 32 && g.n <= 2 && !a.ep_on && ((tiles_r >= 1024 && bpr > 4) || (tiles_r >= 512 && bpr >= 14)) &&
-                             ((one_of_8 && bpr >= 15 && tiles_r < 3500) || (!a.y_bf16 && (one_of_8 || bpr >= 64)));
+    const bool generic_b32 =
+        g.B == 32 && g.n <= 2 &&
+        ((!a.ep_on && ((tiles_r >= 1024 && bpr > 4) || (tiles_r >= 512 && bpr >= 14)) &&
+          ((one_of_8 && bpr >= 15 && tiles_r < 3500) || (!a.y_bf16 && (one_of_8 || bpr >= 64)))) ||
+         (one_of_8 && bpr >= 15 && ((xcd_groups > 64 && xcd_groups <= 128) || (tiles_r >= 16000 && bpr >= 45))));
     // Forced narrow strips and the split by four exist here too (1, 2 and 8, 9); any other forced shape but the
     // generic one does not apply and leaves the choice to the rule.
     const bool forced_r = force_shape == CRISP_SHAPE_REG_NARROW || force_shape == CRISP_SHAPE_REG_SPLIT4 ||

@@ -147,3 +147,29 @@ def test_choice_with_32_row_blocks(case, family):
     assert out[0][0] == family and out[1][0] == "generic"
     # the same products in another order, and for bf16 the roundings of either (1.66e-3 each of a result)
     assert float((out[0][1] - out[1][1]).norm() / out[1][1].norm()) <= (2 * 1.66e-3 if bf16 else 1e-5)
+
+
+# 1:8, 32x32 blocks, long rows: the generic kernel's wide strips are ahead with a layer tail as well (us of the register
+# kernels / generic: 130 / 104, 221 / 184, 50 / 42), but not on fewer tiles, more tiles or shorter rows
+@pytest.mark.parametrize("case,ep,family", [((64, 4080, 65793, 0.4, 1), 1, "generic"), ((64, 3848, 69759, 0.75, 0), 1, "generic"),
+                                            ((64, 1224, 68186, 0.53, 1), 1, "generic"), ((64, 4080, 40001, 0.4, 1), 1, "reg"),
+                                            ((64, 1224, 68186, 0.25, 1), 1, "reg"), ((128, 1224, 68186, 0.53, 1), 1, "reg")], ids=str)
+def test_choice_for_one_of_eight(case, ep, family):
+    S, K, N, dens, bf16 = case
+    g = torch.Generator(device="cuda").manual_seed(S)
+    layer = crisp.alloc_layer(crisp.layer_desc(S, K, 1, 8, 32, dens, crisp.SAL_MAG))
+    W = (torch.randn((S, K), generator=g, device="cuda") * 0.05).to(torch.bfloat16).view(torch.int16)
+    crisp.prune_and_pack(layer, W, None)
+    ld = (N + 7) // 8 * 8
+    X = torch.randn((K, ld), generator=g, device="cuda").to(torch.bfloat16).view(torch.int16)
+    sc, bs = torch.rand(S, generator=g, device="cuda") + 0.5, torch.randn(S, generator=g, device="cuda")
+    out = []
+    for shape in (crisp.SHAPE_AUTO, 4):
+        Y = torch.full((S, ld), float("nan"), dtype=torch.bfloat16 if bf16 else torch.float32, device="cuda")
+        code = crisp.crisp_spmm_forced(layer.desc, layer.row_ptr, layer.col_idx, layer.vals, layer.idx_words, X, N, ld, Y, ld,
+                                       crisp.Y_BF16 if bf16 else crisp.Y_F32, crisp.epilogue(sc, bs, None, 0, True) if ep else None, shape)
+        torch.cuda.synchronize()
+        out.append((crisp.kernel_code_fields(code)["family"], Y[:, :N].float()))
+    assert out[0][0] == family and out[1][0] == "generic"
+    # the same products in another order, and for bf16 the roundings of either (1.66e-3 each of a result)
+    assert float((out[0][1] - out[1][1]).norm() / out[1][1].norm()) <= (2 * 1.66e-3 if bf16 else 1e-5)
