@@ -78,3 +78,29 @@ def test_infinite_activation_outside_the_kept_blocks_stays_outside(K):
             X[b * 16:(b + 1) * 16] = 0x7F80
     out, _ = _run(layer, dev(np.ascontiguousarray(X)), N, N, S, crisp.Y_F32)
     check_product(out, Yref, Aref, crisp.Y_F32, "infinite rows")
+
+
+@pytest.mark.parametrize("S,K,N,dens", [(100, 96, 131, 0.5), (48, 200, 77, 1.0), (64, 64, 128, 0.3), (21, 48, 3, 1.0)])
+@pytest.mark.parametrize("parts", ["scale", "bias", "residual", "relu", "all"])
+def test_tail_of_rows_that_end_inside_a_lane(S, K, N, dens, parts):
+    """Every part of the layer tail alone and all together, both output types: the same fp32 steps in their order, and nothing
+    taken from the residual's columns past the last one (NaN there)."""
+    g = torch.Generator(device="cuda").manual_seed(S + N)
+    layer = crisp.alloc_layer(crisp.layer_desc(S, K, 2, 8, 16, dens, crisp.SAL_MAG))
+    crisp.prune_and_pack(layer, torch.randn((S, K), generator=g, device="cuda").to(torch.bfloat16).view(torch.int16), None)
+    ld = (N + 7) // 8 * 8
+    X = torch.randn((K, ld), generator=g, device="cuda").to(torch.bfloat16).view(torch.int16)
+    plain = torch.from_numpy(_run(layer, X, N, ld, S, crisp.Y_F32)[0]).cuda().float()
+    scale, bias = torch.rand(S, generator=g, device="cuda") + 0.5, torch.randn(S, generator=g, device="cuda")
+    for yd, dtype in ((crisp.Y_F32, torch.float32), (crisp.Y_BF16, torch.bfloat16)):
+        res = torch.full((S, ld + 8), float("nan"), dtype=dtype, device="cuda")
+        res[:, :N] = torch.randn((S, N), generator=g, device="cuda").to(dtype)
+        use = {p: parts in (p, "all") for p in ("scale", "bias", "residual", "relu")}
+        want = plain * scale[:, None] if use["scale"] else plain.clone()
+        want = want + bias[:, None] if use["bias"] else want
+        want = want + res[:, :N].float() if use["residual"] else want
+        want = (torch.relu(want) if use["relu"] else want).to(dtype).double()
+        ep = crisp.epilogue(scale if use["scale"] else None, bias if use["bias"] else None, res if use["residual"] else None,
+                            ld + 8 if use["residual"] else 0, use["relu"])
+        out, _ = _run(layer, X, N, ld, S, yd, ep)
+        assert (torch.from_numpy(out).cuda() == want).all(), (parts, dtype)
