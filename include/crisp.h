@@ -318,8 +318,9 @@ CRISP_API crisp_status crisp_spmm(const crisp_layer_desc *desc, const int32_t *r
  * taps and up to four block-rows (chosen for dense multi-row layers).  Channel counts that are
  * no multiple of 64 with 64x64 blocks, even W and even Ho*Wo run in a kernel that keeps the input
  * patch of 1024 output positions in LDS.  ws, ws_bytes: reserved, ignored.
- * With C % B == 0, W >= 4, pad < kh, up to 32 taps and enough columns a kernel takes over that stages, for a run of
- * output positions, the input positions it touches, whatever the stride and the width.
+ * With C % 8 == 0, W >= 4, pad < kh, up to 31 taps, at most 512 block columns, batch*H*W < 2^26 and enough columns a
+ * kernel takes over that stages, for a run of output positions, the input positions it touches, whatever the stride and
+ * the width.
  * Anything else returns CRISP_EUNSUPPORTED (use crisp_im2col + crisp_spmm).
  * Errors: EINVAL, ESHAPE, EALIGN, EUNSUPPORTED, EDEVICE.
  */

@@ -1,4 +1,4 @@
-// Hybrid-sparse convolution from an input window in LDS: any filter of up to 32 taps, any stride, any width.
+// Hybrid-sparse convolution from an input window in LDS: any filter of up to 31 taps, any stride, any width.
 //
 // conv_lds.h stages a patch of whole output rows with its halo, 64 channels at a time, for waves of 64 rows x 64
 // columns; each wave builds the matrix core's weight operand of a kept block for 64 output positions.  Here
@@ -13,7 +13,7 @@
 // LDS layout: row of CC channels (+ 16 bytes) per input position, even positions first, then the odd ones.  A lane owns
 // two neighbouring output columns (dword stores); at stride 1 the lanes' positions for one of the two are then
 // neighbouring rows, an odd number of 16-byte units apart: conflict-free 16-byte reads (4.3 clocks per wave and
-// request against 8.5 with positions in order, measured).
+// request against 8.5 with positions in order, measured).  At stride 2 they are every second row: half of the banks, two ways.
 #pragma once
 #include "conv_tile_plan.h"
 #include "spmm_reg.h"

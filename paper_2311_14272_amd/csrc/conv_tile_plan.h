@@ -8,7 +8,7 @@ namespace crisp {
 
 constexpr int CONV_TILE_MAX_LDS = 152 * 1024;    // of 160 KB: the selector table of 4:8 is beside it
 constexpr int CONV_TILE_MAX_KB = 512;            // block columns (taps x channel blocks)
-constexpr int CONV_TILE_MAX_TAPS = 32;           // bits of a lane's tap mask
+constexpr int CONV_TILE_MAX_TAPS = 32;           // bits of a lane's tap mask; the last one is no tap: an octet that lies elsewhere
 constexpr int CONV_TILE_MAX_WINDOW = 4096;       // positions staged at once
 
 // The convolution as the schedule sees it.
@@ -136,6 +136,7 @@ inline bool conv_tile_covers(const ConvShape& a) {
 // Waves of a compute unit that the kernel's registers leave room for.  2:4 with 64x64 blocks has two packed slices of 20
 // registers on their way: three waves per SIMD would spill 14 to 54 of 168 registers (256 x 10400 x 20384: 190 us, with two
 // waves 104; fifteen such convolutions with channels that are no multiple of 64 at 0.57 of the time, twenty others at 0.98).
+// 3:4, 4:4 and 8:8 spill 6 to 17 of 168: with two waves and nothing spilled 1.000 of the time over 900, so three stay.
 constexpr int conv_tile_waves(int n, int m, int B, int NC2) { return NC2 == 2 || (n == 2 && m == 4 && B == 64) ? 8 : 12; }
 
 // What a schedule has a compute unit do, in clocks.

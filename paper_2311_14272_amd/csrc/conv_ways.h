@@ -16,7 +16,9 @@ namespace crisp {
 // X with rows of equal length run at 0.764 of the time that X takes (geometric mean; 0.740 with the best of all ways each
 // time), five are slower by more than 5 % (1.15 the worst: 986 x 1584 x 20384 2:8 78 / 90 us); the 1480 planned fused at
 // 0.878 of the older fused kernels' (0.847 at best), three are slower (669 x 4032 x 9408 3:4 103 / 137 us).  With margins of
-// 1.1 the means are 0.01 lower and ten times as many are slower, up to 1.5.
+// 1.1 the means are 0.01 lower and ten times as many are slower, up to 1.5.  Where K is short (8 or 16 channels, K <= 192) the
+// estimates are at their worst: 69 that run in the window kernel at 0.72, seven slower by more than 5 % (480 x 144 x 68992 4:4
+// 35 / 46 us); a further margin of 1.25 there loses more (0.806 -> 0.827 over 900) than it mends (ten slower by a tenth, then eight).
 constexpr double WINDOW_OVER_X = 1.25, REG_OVER_X = 1.25, WINDOW_OVER_FUSED = 1.25;
 // ... and once more where block-rows differ in length: a workgroup of the window kernel lasts as long as its longest row, X
 // is multiplied by a kernel that deals the blocks evenly.  1000 planned through X and pruned over the whole grid, half of
