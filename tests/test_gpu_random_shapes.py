@@ -316,15 +316,16 @@ def _draw_bag_layer(rng, i, common):
         return synth.LayerSpec("L%d" % i, S, K, 8, n, m, B, dens, salk, 0.05, None, mode)
 
 
-@pytest.mark.parametrize("seed", [141])
-def test_random_layer_bags(seed):
+@pytest.mark.parametrize("seed,edges,bags,most", [(141, (32, 64), 30, 23), (142, (16,), 5, 60)])
+def test_random_layer_bags(seed, edges, bags, most):
     """crisp_select_pack_batch over random bags of layers (several launch groups, uneven-row layers, given
-    saliencies full of ties), then crisp_global_budget on the bag's block scores: all bit for bit."""
+    saliencies full of ties), then crisp_global_budget on the bag's block scores: all bit for bit.  edges: block sizes that
+    most of a bag's layers share; 16 x 16 blocks come in bags of more layers than their workgroups have threads."""
     rng = np.random.default_rng(seed)
     fails = []
-    for bag in range(30):
-        common = (int(rng.choice([32, 64])), int(rng.choice([4, 8])), int(rng.choice([synth.SAL_GRAD, synth.SAL_MAG])))
-        cases = [_draw_bag_layer(rng, i, common) for i in range(int(rng.integers(1, 24)))]
+    for bag in range(bags):
+        common = (int(rng.choice(list(edges))), int(rng.choice([4, 8])), int(rng.choice([synth.SAL_GRAD, synth.SAL_MAG])))
+        cases = [_draw_bag_layer(rng, i, common) for i in range(int(rng.integers(1 if most < 24 else 30, most + 1)))]
         print("bag", bag, [(L.S, L.K, L.n, L.m, L.B, L.density, L.sal_kind, L.select_mode) for L in cases], flush=True)
         layers, Ws, TGs, expect = [], [], [], []
         for L in cases:
