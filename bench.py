@@ -86,8 +86,8 @@ def parse():
 # value = (bytes per launch, file under profiles/ that holds the counter rows).  A kernel without an entry reports null.
 TRAFFIC = {
     # (the two kernels whose shares of the step are within a few percent of each other; whichever the warm-up passes find)
-    ("c5", "reg 4:8 B64 shape1 conv0 dense-mfma"): (199492718, "profiles/bench_c5_kernels.txt"),
-    ("c5", "reg 2:8 B64 shape0 conv0 sparse-mfma"): (243615633, "profiles/bench_c5_kernels.txt"),
+    ("c5", "reg 4:8 B64 shape1 conv0 dense-mfma"): (199567970, "profiles/bench_c5_kernels.txt"),
+    ("c5", "reg 2:8 B64 shape0 conv0 sparse-mfma"): (243624695, "profiles/bench_c5_kernels.txt"),
     # configs 1-4 as the workload of the line: bytes = (2.0 * FETCH_SIZE + 1.0 * WRITE_SIZE) KiB of the dominant layer's kernel
     ("c1", "reg 2:4 B32 shape2 conv0 sparse-mfma"): (int((2.0 * 4220.0 + 1568.0) * 1024), "profiles/bench_c1_kernels.txt"),
     ("c2", "reg 1:4 B64 shape1 conv0 sparse-mfma"): (int((2.0 * 1753.6 + 12544.0) * 1024), "profiles/bench_c2_kernels.txt"),
